@@ -442,7 +442,7 @@ def _rule(degree, n):
     """Nodes' harmonics [Q, n^2] and weights [Q] of a product rule exact to ``degree``."""
     z, w = np.polynomial.legendre.leggauss(degree // 2 + 1)
     m = degree + 1
-    ph = np.arange(m) * 2 * np.pi / m
+    ph = (np.arange(m) + 0.5) * 2 * np.pi / m
     r = np.sqrt(1 - z * z)
     d = np.stack([r[:, None] * np.cos(ph), r[:, None] * np.sin(ph), z[:, None] + 0 * ph], -1).reshape(-1, 3)
     t = torch.as_tensor(d, device="cuda")
