@@ -238,12 +238,89 @@ def parity_groups(n, adjoint, ng=N_GROUPS):
 
 
 def forward_groups(n, ng=N_GROUPS):
-    return parity_groups(n, False, ng)
+    return order_groups(n, ng) if n >= LAT_MIN_BANDS else parity_groups(n, False, ng)
 
 
 def adjoint_groups(n, ng=N_GROUPS):
     """Also the canonical grouping of the backward's sums."""
-    return parity_groups(n, True, ng)
+    return order_groups(n, ng) if n >= LAT_MIN_BANDS else parity_groups(n, True, ng)
+
+
+# ------------------------------------------------ products through latitudes
+
+LAT_MIN_BANDS = 6  # products through latitudes from this band count up (see shv_lat.h)
+
+
+def order_groups(n, ng=N_GROUPS):
+    """Output groups of a product through latitudes: whole orders |m|, since
+    an order's coefficients share its Fourier product.  Cost of order m: its
+    complex terms at every latitude plus its transposed transform; the orders
+    are assigned in decreasing cost to the least loaded group."""
+    cost = {m: (2 * n - 1 - m) * 4 * ((3 * n - 1) // 2) + 5 * 2 * (n - m) for m in range(1, n)}
+    cost[0] = (2 * n - 1) * 2 * ((3 * n - 1) // 2) + 5 * n
+    load, grp = [0] * ng, {}
+    for m in sorted(cost, key=lambda m: -cost[m]):
+        g = load.index(min(load))
+        grp[m] = g
+        load[g] += cost[m]
+    return [sorted(i for i in range(n * n) if grp[abs(lm(i)[1])] == g) for g in range(ng)]
+
+
+def lat_rows(n):
+    """The Gauss-Legendre latitudes z > 0 of the rule that integrates the
+    triple products of n bands exactly (degree 3 n - 3), and z = 0 where the
+    rule has it: one row each, entries (m, l) m-major,
+      w^(1/3) sqrt(4 pi) N_lm P_l^m(z),
+    N_lm P_l^m being y_lm without its azimuth function (and without the sqrt 2
+    that has for m > 0).  The transform of each factor and the transposed
+    transform carry w^(1/3) each, so a product carries the weight w = 2 (w / 2):
+    the projection of twice the product."""
+    zs, ws = np.polynomial.legendre.leggauss((3 * n - 3) // 2 + 1)
+
+    def row(z, w):
+        out = []
+        r = math.sqrt(1 - z * z)
+        for m in range(n):
+            p = math.sqrt((2 * m + 1) * math.prod((2 * i - 1) / (2 * i) for i in range(1, m + 1))) * r ** m
+            prev, cur = 0.0, p
+            for l in range(m, n):
+                if l > m:
+                    a = math.sqrt((4 * l * l - 1) / (l * l - m * m))
+                    b = math.sqrt(((l - 1) ** 2 - m * m) / (4 * (l - 1) ** 2 - 1)) if l > m + 1 else 0.0
+                    prev, cur = cur, a * (z * cur - b * prev)
+                out.append(w ** (1 / 3) * cur)
+        return out + [0.0] * (-len(out) % 4)
+
+    pairs = [row(z, w) for z, w in zip(zs, ws) if z > 1e-9]
+    eq = [row(0.0, w) for z, w in zip(zs, ws) if abs(z) <= 1e-9]
+    return pairs, eq
+
+
+def emit_lat(L):
+    lamb = recurrence_constants()[1]
+    for name, f in (("SHV_LAT_LAM", lambda m: (1.0 if m == 0 else math.sqrt(0.5)) / math.sqrt(4 * PI)),
+                    ("SHV_LAT_LAMI", lambda m: 1.0 if m == 0 else math.sqrt(2.0))):
+        L.append(f"// LAMBDA[l][m] times {'the scale of a coefficient' if name.endswith('M') else '1 / (sqrt(4 pi) scale)'}.")
+        L.append(f"static constexpr float {name}[{MAX_BANDS}][{MAX_BANDS}] = {{")
+        for l in range(MAX_BANDS):
+            L.append("  {" + ", ".join(flit(lamb[l][m] * f(m)) for m in range(MAX_BANDS)) + "},")
+        L.append("};")
+    L.append("static constexpr float SHV_LAT_INV[2] = {" + flit(math.sqrt(4 * PI)) + ", " + flit(math.sqrt(8 * PI))
+             + "};  // 1 / scale, m = 0 and m != 0")
+    L.append("static constexpr float SHV_LAT_SCALE[2] = {" + flit(1 / math.sqrt(4 * PI)) + ", "
+             + flit(1 / math.sqrt(8 * PI)) + "};")
+    L.append("// Products through latitudes (shv_lat.h): the rows of the pairs +-z, then of the equator.")
+    for n in range(LAT_MIN_BANDS, MAX_BANDS + 1):
+        pairs, eq = lat_rows(n)
+        vals = [v for r in pairs + eq for v in r]
+        L.append(f"static constexpr int SHV_LAT_PAIRS_{n} = {len(pairs)}, SHV_LAT_EQ_{n} = {len(eq)};")
+        L.append(f"static constexpr float shv_lat_rows_{n}[{len(vals)}] = {{" + ",".join(flit(v) for v in vals) + "};")
+        for name, grs in (("SHV_FGRP", forward_groups(n)), ("SHV_GRP", adjoint_groups(n))):
+            gid = [0] * (n * n)
+            for g, members in enumerate(grs):
+                for i in members:
+                    gid[i] = g
+            L.append(f"static constexpr unsigned char {name}_{n}[{n * n}] = {{" + ",".join(map(str, gid)) + "};")
 
 
 # ----------------------------------------------------------------- emission
@@ -295,6 +372,20 @@ def transfer_support(n):
     return [i for i in range(n * n) if clamped_cosine(lm(i)[0]) != 0.0]
 
 
+def mtable(N, C):
+    """Sparse table grouped by (j, k) for building M(L)_jk = sum_i L_i C_ijk."""
+    rows = [[] for _ in range(N * N)]
+    for (i, j, k), c in C.items():
+        rows[j * N + k].append((i, c))
+    ptr, ent_i, ent_c = [0], [], []
+    for r in rows:
+        for i, c in sorted(r):
+            ent_i.append(i)
+            ent_c.append(c)
+        ptr.append(len(ent_i))
+    return ptr, ent_i, ent_c
+
+
 def emit_gaunt(path):
     L = ["// Generated by gen_tables.py: unrolled sparse SH triple products.",
          "// C_ijk = integral y_i y_j y_k from Wigner 3j symbols; straight-line code",
@@ -308,6 +399,9 @@ def emit_gaunt(path):
         sym = sorted((i, j, k) for (i, j, k) in C if j <= k)
         L.append(f"// n = {n}: {nnz} nonzero C_ijk, {len(sym)} with j <= k")
         L.append(f"#define SHV_GAUNT_NNZ_{n} {nnz}")
+        tables.append((n, *mtable(N, C)))
+        if n >= LAT_MIN_BANDS:
+            continue
 
         # o = e * e (symmetric squaring)
         L.append(f"__device__ __forceinline__ void shv_square_{n}(const float* __restrict__ e, float* __restrict__ o) {{")
@@ -412,18 +506,6 @@ def emit_gaunt(path):
                     L.append(f"  eb[{j}] = 0.0f;")
             L.append("}")
 
-        # sparse table grouped by (j, k) for building M(L)_jk = sum_i L_i C_ijk
-        rows = [[] for _ in range(N * N)]
-        for (i, j, k), c in C.items():
-            rows[j * N + k].append((i, c))
-        ptr = [0]
-        ent_i, ent_c = [], []
-        for r in rows:
-            for i, c in sorted(r):
-                ent_i.append(i)
-                ent_c.append(c)
-            ptr.append(len(ent_i))
-        tables.append((n, ptr, ent_i, ent_c))
         L.append("")
 
     L.append("// (j, k)-grouped sparse C for building M(L); CSR over j*N + k.")
@@ -473,6 +555,8 @@ def emit_gaunt(path):
         z, wz = np.polynomial.legendre.leggauss(4 * n)
         L.append(f"__device__ const float shv_quad_z_{n}[{4 * n}] = {{" + ",".join(flit(v) for v in z) + "};")
         L.append(f"__device__ const float shv_quad_w_{n}[{4 * n}] = {{" + ",".join(flit(v) for v in wz) + "};")
+    L.append("")
+    emit_lat(L)
     L.append("")
     for n in range(1, MAX_BANDS + 1):
         supp = transfer_support(n)

@@ -10,7 +10,9 @@
 //          sphere are Gaussian with variance |G|^2 / (4 pi); it gives a = b)
 //   E_{j+1} = E_j * E_j  (k truncated triple-product squarings, Eqs. 6-7)
 //   V   = exp(c) E_k
-// The squaring is straight-line generated code (coefficients are literals).
+// Up to 5 bands the squaring is straight-line generated code (coefficients are
+// literals), above it goes through latitudes (shv_lat.h), E_j being scaled as
+// described there in registers and in the saved state.
 // Saved for the adjoint, coefficient-major: row 0 = c, rows 1 + j*N + i = E_j[i].
 //
 // The forward kernels also sum the sphere-chunk partials of F' in a fixed
@@ -27,6 +29,7 @@
 #pragma once
 
 #include "shv_batch.h"
+#include "shv_lat.h"
 #include "shv_launch.h"
 #include "shv_shade_common.h"
 #include "shvis.h"
@@ -34,55 +37,38 @@
 namespace shv {
 
 
-template <int NB>
-__device__ __forceinline__ void square(const float* e, float* o);
-template <int NB>
-__device__ __forceinline__ void square_adj(const float* ob, const float* e, float* eb);
-
-#define SHV_SQ(n)                                                                                    \
-  template <>                                                                                        \
-  __device__ __forceinline__ void square<n>(const float* e, float* o) { shv_square_##n(e, o); }      \
-  template <>                                                                                        \
-  __device__ __forceinline__ void square_adj<n>(const float* ob, const float* e, float* eb) {        \
-    shv_square_adj_##n(ob, e, eb);                                                                   \
-  }
-SHV_SQ(1)
-SHV_SQ(2)
-SHV_SQ(3)
-SHV_SQ(4)
-SHV_SQ(5)
-SHV_SQ(6)
-SHV_SQ(7)
-SHV_SQ(8)
-#undef SHV_SQ
-
-// Group g of the output coefficients of one squaring (see the generator).
+// o = e * e and eb = 2 (ob * e), whole (G = -1) or the outputs of group G.
+// Up to 5 bands by the generated sparse contractions, above through latitudes
+// (shv_lat.h; e, ob and the results are then scaled as described there).
 template <int NB, int G>
-struct SqGroup;
-#define SHV_SQG(n, g)                                                                                        \
+struct SqGroup {
+  static __device__ __forceinline__ void square(const float (&e)[NB * NB], float (&o)[NB * NB]) {
+    lat_product<NB, G, true>(e, e, o);
+  }
+  static __device__ __forceinline__ void adj(const float (&ob)[NB * NB], const float (&e)[NB * NB],
+                                             float (&eb)[NB * NB]) {
+    lat_product<NB, G, false>(e, ob, eb);
+  }
+};
+#define SHV_SQG(n, g, suffix)                                                                                \
   template <>                                                                                                \
   struct SqGroup<n, g> {                                                                                     \
-    static __device__ __forceinline__ void square(const float* e, float* o) { shv_square_##n##_g##g(e, o); } \
+    static __device__ __forceinline__ void square(const float* e, float* o) { shv_square_##suffix(e, o); }   \
     static __device__ __forceinline__ void adj(const float* ob, const float* e, float* eb) {                 \
-      shv_square_adj_##n##_g##g(ob, e, eb);                                                                  \
+      shv_square_adj_##suffix(ob, e, eb);                                                                    \
     }                                                                                                        \
   };
-#define SHV_SQG4(n) SHV_SQG(n, 0) SHV_SQG(n, 1) SHV_SQG(n, 2) SHV_SQG(n, 3)
-SHV_SQG4(1)
-SHV_SQG4(2)
-SHV_SQG4(3)
-SHV_SQG4(4)
-SHV_SQG4(5)
-SHV_SQG4(6)
-SHV_SQG4(7)
-SHV_SQG4(8)
-#undef SHV_SQG4
+#define SHV_SQG5(n) SHV_SQG(n, -1, n) SHV_SQG(n, 0, n##_g0) SHV_SQG(n, 1, n##_g1) SHV_SQG(n, 2, n##_g2) SHV_SQG(n, 3, n##_g3)
+SHV_SQG5(1)
+SHV_SQG5(2)
+SHV_SQG5(3)
+SHV_SQG5(4)
+SHV_SQG5(5)
+#undef SHV_SQG5
 #undef SHV_SQG
 
 // Output group of coefficient i: in the adjoint squaring (and the canonical
 // grouping of the backward's sums), and in the forward squaring.
-template <int NB>
-__device__ __forceinline__ constexpr int group_of(int i);
 template <int NB>
 __device__ __forceinline__ constexpr int fgroup_of(int i);
 #define SHV_GOF(n)                                                                          \
@@ -147,22 +133,33 @@ __device__ __forceinline__ float cbar_canonical(const float* vb, const float* v)
   return ((part[0] + part[1]) + part[2]) + part[3];
 }
 
+// eps LAMBDA_i, times the coefficient's scale where products go through latitudes.
+template <int NB>
+__device__ __forceinline__ float coef_weight(int i) {
+  if constexpr (!Lat<NB>::USE) return coef_lambda(i);
+  int l = 0;
+  while ((l + 1) * (l + 1) <= i) ++l;
+  const int m = i - l * l - l;
+  return SHV_LAT_LAM[l][m < 0 ? -m : m];
+}
+
 // E_0 from the summed F' of one receiver (in place): returns c.
 template <int NB>
 __device__ __forceinline__ float exp_prologue(float (&E)[NB * NB], float eps, int k) {
   constexpr int N = NB * NB;
 #pragma unroll
-  for (int i = 0; i < N; ++i) E[i] *= eps * coef_lambda(i);
-  const float c = E[0] * SHV_INV_SQRT_4PI;
+  for (int i = 0; i < N; ++i) E[i] *= eps * coef_weight<NB>(i);
+  const float c = Lat<NB>::USE ? E[0] : E[0] * SHV_INV_SQRT_4PI;
   const float scale = __builtin_ldexpf(1.0f, -k);
-  float sig = 0.0f;
+  float sig = 0.0f, sigm = 0.0f;  // scaled: sums over m = 0 and m != 0, |G|^2 / (8 pi) = sig / 2 + sigm
 #pragma unroll
   for (int i = 1; i < N; ++i) {
     E[i] *= scale;
-    sig = fmaf(E[i], E[i], sig);
+    if (Lat<NB>::USE && !lat_zonal(i)) sigm = fmaf(E[i], E[i], sigm);
+    else sig = fmaf(E[i], E[i], sig);
   }
-  const float a = expf(sig * SHV_INV_8PI);
-  E[0] = a * SHV_SQRT_4PI;
+  const float a = expf(Lat<NB>::USE ? fmaf(0.5f, sig, sigm) : sig * SHV_INV_8PI);
+  E[0] = a * one_coef<NB>();
 #pragma unroll
   for (int i = 1; i < N; ++i) E[i] *= a;
   return c;
@@ -175,17 +172,20 @@ template <int NB, class Keep>
 __device__ __forceinline__ void exp_epilogue(float (&E)[NB * NB], const float (&Eb)[NB * NB], float cbar, float eps,
                                              int k, int64_t P, int64_t p, float* __restrict__ Wout, Keep keep) {
   constexpr int N = NB * NB;
-  const float a = E[0] * SHV_INV_SQRT_4PI;
+  constexpr bool LAT = Lat<NB>::USE;
+  const float a = LAT ? E[0] : E[0] * SHV_INV_SQRT_4PI;
   const float inva = 1.0f / a;
-  float dot = SHV_SQRT_4PI * Eb[0];
+  // Gbar_i = a (Ebar_i + G_i / (4 pi) (sqrt(4 pi) Ebar_0 + sum_j Ebar_j G_j));
+  // scaled, sqrt(4 pi) times the bracket is Ebar_0 + sum_j (2 or, at m = 0, 1) Ebar_j G_j.
+  float dot = LAT ? Eb[0] : SHV_SQRT_4PI * Eb[0], dotm = 0.0f;
 #pragma unroll
   for (int i = 1; i < N; ++i) {
     E[i] *= inva;  // G_i
-    dot = fmaf(Eb[i], E[i], dot);
+    if (LAT && !lat_zonal(i)) dotm = fmaf(Eb[i], E[i], dotm);
+    else dot = fmaf(Eb[i], E[i], dot);
   }
-  // Gbar_i = a (Ebar_i + G_i / (4 pi) (sqrt(4 pi) Ebar_0 + sum_j Ebar_j G_j))
   const float scale = __builtin_ldexpf(1.0f, -k);
-  const float kdot = dot * SHV_INV_4PI;
+  const float kdot = LAT ? fmaf(2.0f, dotm, dot) : dot * SHV_INV_4PI;
   if (keep(0)) Wout[p] = eps * SHV_LAMBDA[0][0] * cbar * SHV_INV_SQRT_4PI;
 #pragma unroll
   for (int l = 1; l < NB; ++l) {
@@ -194,7 +194,8 @@ __device__ __forceinline__ void exp_epilogue(float (&E)[NB * NB], const float (&
       const int i = idx(l, m);
       if (!keep(i)) continue;
       const float gb = a * fmaf(E[i], kdot, Eb[i]);
-      Wout[(int64_t)i * P + p] = eps * SHV_LAMBDA[l][m < 0 ? -m : m] * scale * gb;
+      const float lam = LAT ? SHV_LAT_LAMI[l][m < 0 ? -m : m] : SHV_LAMBDA[l][m < 0 ? -m : m];
+      Wout[(int64_t)i * P + p] = eps * lam * scale * gb;
     }
   }
 }
@@ -254,14 +255,14 @@ __device__ __forceinline__ void exp_fwd1_item(const float* __restrict__ Fpart, i
 #pragma unroll
       for (int i = 0; i < N; ++i) dst[(int64_t)i * P] = E[i];
     }
-    square<NB>(E, O);
+    SqGroup<NB, -1>::square(E, O);
 #pragma unroll
     for (int i = 0; i < N; ++i) E[i] = O[i];
   }
   const float ec = expf(c);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    E[i] = ec * E[i];
+    E[i] = (ec * E[i]) * coef_inv<NB>(i);
     if (ok) vis[(int64_t)i * P + p] = E[i];
   }
   if constexpr (SHADE) {
@@ -345,14 +346,14 @@ __device__ __forceinline__ void exp_bwd1_item(const float* __restrict__ gIn, con
   const float cbar = cbar_canonical<NB>(Eb, E);  // d/dc of exp(c) E_k . Vbar = V . Vbar
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    if (k == 0) E[i] = E[i] / ec;  // E_0 itself when there is no squaring
-    Eb[i] = ec * Eb[i];
+    if (k == 0) E[i] = (E[i] / ec) * coef_scale<NB>(i);  // E_0 itself when there is no squaring
+    Eb[i] = (ec * Eb[i]) * cot_scale<NB>(i);
   }
   for (int j = k - 1; j >= 0; --j) {
     const float* src = saved + (int64_t)(1 + j * N) * P + p;
 #pragma unroll
     for (int i = 0; i < N; ++i) E[i] = src[(int64_t)i * P];
-    square_adj<NB>(Eb, E, T);  // Ebar_j = 2 (Ebar_{j+1} * E_j)
+    SqGroup<NB, -1>::adj(Eb, E, T);  // Ebar_j = 2 (Ebar_{j+1} * E_j)
 #pragma unroll
     for (int i = 0; i < N; ++i) Eb[i] = T[i];
   }
@@ -360,7 +361,7 @@ __device__ __forceinline__ void exp_bwd1_item(const float* __restrict__ gIn, con
 }
 
 template <int NB, bool SHADE>
-__global__ __launch_bounds__(SHV_BLOCK) void k_exp_bwd(const float* __restrict__ gIn, const float* __restrict__ vis,
+__global__ __launch_bounds__(SHV_BLOCK, NB <= 6 ? 2 : 1) void k_exp_bwd(const float* __restrict__ gIn, const float* __restrict__ vis,
                                                        const float* __restrict__ saved, int64_t P, float eps, int k,
                                                        float* __restrict__ Wout, ShadeArgs sa) {
   if constexpr (SHADE) {
@@ -421,7 +422,7 @@ __device__ __forceinline__ void exp_fwd_group(float (*X)[NB * NB][64], float (*B
   }
   const float ec = expf(c);
 #pragma unroll
-  for (int i = 0; i < N; ++i) E[i] = ec * E[i];  // V, complete in every wave
+  for (int i = 0; i < N; ++i) E[i] = (ec * E[i]) * coef_inv<NB>(i);  // V, complete in every wave
   if (ok) {
 #pragma unroll
     for (int i = 0; i < N; ++i)
@@ -576,10 +577,10 @@ __device__ __forceinline__ void exp_bwd_group(float (*X)[NB * NB][64], Bwd4Share
     if (sa.Lpart) tile_light_partial<NB>(LT, sa.Lpart + bx * N);
   }
 #pragma unroll
-  for (int i = 0; i < N; ++i) Eb[i] = ec * X[1][i][lane];
+  for (int i = 0; i < N; ++i) Eb[i] = (ec * X[1][i][lane]) * cot_scale<NB>(i);
   if (k == 0) {  // E_0 = V / exp(c) when there is no squaring; the loop below loads E_j otherwise
 #pragma unroll
-    for (int i = 0; i < N; ++i) E[i] = X[0][i][lane] / ec;
+    for (int i = 0; i < N; ++i) E[i] = (X[0][i][lane] / ec) * coef_scale<NB>(i);
   }
   const float cbar = ((sh.Cb[0][lane] + sh.Cb[1][lane]) + sh.Cb[2][lane]) + sh.Cb[3][lane];
   // This wave's group of E_j is loaded one step ahead, so the loads are in
@@ -719,7 +720,7 @@ __global__ __launch_bounds__(SHV_BLOCK) void k_batch_exp_fwd(const char* __restr
 }
 
 template <int NB, bool FOUR>
-__global__ __launch_bounds__(SHV_BLOCK, FOUR ? 2 : 1) void k_batch_exp_bwd(const char* __restrict__ table) {
+__global__ __launch_bounds__(SHV_BLOCK, FOUR || NB <= 6 ? 2 : 1) void k_batch_exp_bwd(const char* __restrict__ table) {
   __shared__ Exp4BwdShared<NB> sh;
   const BatchView v(table);
   const int64_t item = blockIdx.x;

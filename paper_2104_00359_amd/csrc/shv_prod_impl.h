@@ -39,13 +39,15 @@
 namespace shv {
 
 // h = LAMBDA (.) F' of one pair: the same recurrence and products as the pair
-// forward kernel, each coefficient scaled by its LAMBDA[l][|m|].
+// forward kernel, each coefficient scaled by its LAMBDA[l][|m|] (and by its
+// scale where products go through latitudes).
 template <int NB>
 __device__ __forceinline__ void blocker_vec(const PairGeom& G, float (&h)[NB * NB]) {
   float R[NB + 1], g[NB], C[NB], Sn[NB];
   legendre_resid<NB>(G.t, G.u, R);
   cap_zonal<NB>(G.u, R, g);
   cs_powers<NB>(G.x, G.y, C, Sn);
+  constexpr const auto& LAM = Lat<NB>::USE ? SHV_LAT_LAM : SHV_LAMBDA;
 #pragma unroll
   for (int m = 0; m < NB; ++m) {
     float r2 = 0.0f, r1 = 1.0f;
@@ -61,13 +63,23 @@ __device__ __forceinline__ void blocker_vec(const PairGeom& G, float (&h)[NB * N
         u = g[l] * r;
       }
       if (m == 0) {
-        h[idx(l, 0)] = SHV_LAMBDA[l][0] * u;
+        h[idx(l, 0)] = LAM[l][0] * u;
       } else {
-        h[idx(l, m)] = SHV_LAMBDA[l][m] * (u * C[m]);
-        h[idx(l, -m)] = SHV_LAMBDA[l][m] * (u * Sn[m]);
+        h[idx(l, m)] = LAM[l][m] * (u * C[m]);
+        h[idx(l, -m)] = LAM[l][m] * (u * Sn[m]);
       }
     }
   }
+}
+
+// Group G of 2 (a * b); through latitudes a's mean is multiplied exactly.  The
+// rows stay rolled: two unrolled products and the pair adjoint in four groups
+// leave the instruction cache (adjoint of 20,000 x 128 at 8 bands 1,570 us
+// rolled, 2,320 us unrolled).
+template <int NB, int G>
+__device__ __forceinline__ void prod2(const float (&a)[NB * NB], const float (&b)[NB * NB], float (&o)[NB * NB]) {
+  if constexpr (Lat<NB>::USE) lat_product<NB, G, false, true>(a, b, o);
+  else SqGroup<NB, G>::adj(b, a, o);
 }
 
 template <int NB>
@@ -87,7 +99,7 @@ __device__ __forceinline__ void prod_fwd_group(float (*X)[NB * NB][64], int lane
   const float pz = sel0(ok, pts[2 * P + q]);
   float V[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) V[i] = i == 0 ? SHV_SQRT_4PI : 0.0f;
+  for (int i = 0; i < N; ++i) V[i] = i == 0 ? one_coef<NB>() : 0.0f;
   for (int s = 0; s < S; ++s) {
     if (states && ok) {
       float* dst = states + (int64_t)s * N * P + p;
@@ -97,7 +109,8 @@ __device__ __forceinline__ void prod_fwd_group(float (*X)[NB * NB][64], int lane
     }
     float h[N], T[N];
     blocker_vec<NB>(pair_geom(px, py, pz, sph[s]), h);
-    SqGroup<NB, G>::adj(V, h, T);  // group G of 2 (V * h)
+    if constexpr (Lat<NB>::USE) prod2<NB, G>(V, h, T);
+    else prod2<NB, G>(h, V, T);
     const int b = s & 1;
 #pragma unroll
     for (int i = 0; i < N; ++i)
@@ -109,7 +122,7 @@ __device__ __forceinline__ void prod_fwd_group(float (*X)[NB * NB][64], int lane
   if (vis && ok) {
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      if (group_of<NB>(i) == G) vis[(int64_t)i * P + p] = V[i];
+      if (group_of<NB>(i) == G) vis[(int64_t)i * P + p] = V[i] * coef_inv<NB>(i);
   }
 }
 
@@ -154,7 +167,7 @@ __device__ __forceinline__ void prod_bwd_group(ProdBwdShared<NB>& sh, int lane, 
   // to the sphere sums), the input of the last step, and the next one ahead.
 #pragma unroll
   for (int i = 0; i < N; ++i)
-    if (group_of<NB>(i) == G) sh.Vb[S & 1][i][lane] = sel0(ok, gvis[(int64_t)i * P + q]);
+    if (group_of<NB>(i) == G) sh.Vb[S & 1][i][lane] = sel0(ok, gvis[(int64_t)i * P + q]) * cot_scale<NB>(i);
   float pre[N];
   if (S > 0) {
     const float* src = states + (int64_t)(S - 1) * N * P + q;
@@ -177,7 +190,7 @@ __device__ __forceinline__ void prod_bwd_group(ProdBwdShared<NB>& sh, int lane, 
       Vb[i] = sh.Vb[b ^ 1][i][lane];
       A[i] = sh.Vi[b][i][lane];
     }
-    SqGroup<NB, G>::adj(Vb, A, T);  // group G of 2 (Vb * V_in)
+    prod2<NB, G>(A, Vb, T);  // V_in, Vb
     const PairGeom geo = pair_geom(px, py, pz, sph[s]);
     {
       // This wave's share of the pair weights: W_lm = LAMBDA_lm hbar_lm on
@@ -188,7 +201,7 @@ __device__ __forceinline__ void prod_bwd_group(ProdBwdShared<NB>& sh, int lane, 
 #pragma unroll
         for (int m = -l; m <= l; ++m) {
           const int i = idx(l, m);
-          const float w = group_of<NB>(i) == G ? SHV_LAMBDA[l][m < 0 ? -m : m] * (hbeta * T[i]) : 0.0f;
+          const float w = group_of<NB>(i) == G ? (Lat<NB>::USE ? SHV_LAT_LAMI : SHV_LAMBDA)[l][m < 0 ? -m : m] * (hbeta * T[i]) : 0.0f;
           W[i] = w;
           Wz[i] = w * SHV_RHO[l][m < 0 ? -m : m];
         }
@@ -202,7 +215,7 @@ __device__ __forceinline__ void prod_bwd_group(ProdBwdShared<NB>& sh, int lane, 
       if (lane == 63) gs_row[s] = tot;
     }
     blocker_vec<NB>(geo, A);
-    SqGroup<NB, G>::adj(Vb, A, T);  // group G of 2 (Vb * h)
+    prod2<NB, G>(A, Vb, T);  // h, Vb
 #pragma unroll
     for (int i = 0; i < N; ++i)
       if (group_of<NB>(i) == G) sh.Vb[b][i][lane] = fmaf(hbeta, T[i], Vb[i]);

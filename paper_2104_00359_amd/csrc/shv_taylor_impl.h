@@ -57,8 +57,8 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
   int b = 1;  // next exchange buffer
   float Gv[N], R[N], T[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) Gv[i] = sh.X[0][i][lane] * (eps * coef_lambda(i));
-  const float c = Gv[0] * SHV_INV_SQRT_4PI;
+  for (int i = 0; i < N; ++i) Gv[i] = sh.X[0][i][lane] * (eps * coef_weight<NB>(i));
+  const float c = Lat<NB>::USE ? Gv[0] : Gv[0] * SHV_INV_SQRT_4PI;
   const float scale = __builtin_ldexpf(1.0f, -k);
   Gv[0] = 0.0f;
 #pragma unroll
@@ -72,7 +72,7 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
   }
   // Horner: R_K = 1, R_{j-1} = 1 + (R_j * G) / j.
 #pragma unroll
-  for (int i = 0; i < N; ++i) R[i] = i == 0 ? SHV_SQRT_4PI : 0.0f;
+  for (int i = 0; i < N; ++i) R[i] = i == 0 ? one_coef<NB>() : 0.0f;
   for (int j = K; j >= 1; --j) {
     if (j < K && saved && ok) {
       float* dst = grow + (int64_t)j * N * P;
@@ -80,11 +80,13 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
       for (int i = 0; i < N; ++i)
         if (group_of<NB>(i) == G) dst[(int64_t)i * P] = R[i];
     }
-    SqGroup<NB, G>::adj(R, Gv, T);  // group G of 2 (R_j * G)
+    // group G of 2 (R_j * G); through latitudes the second factor's mean is exact
+    if constexpr (Lat<NB>::USE) SqGroup<NB, G>::adj(Gv, R, T);
+    else SqGroup<NB, G>::adj(R, Gv, T);
     const float h = 0.5f / (float)j;
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      if (group_of<NB>(i) == G) sh.X[b][i][lane] = i == 0 ? fmaf(h, T[i], SHV_SQRT_4PI) : h * T[i];
+      if (group_of<NB>(i) == G) sh.X[b][i][lane] = i == 0 ? fmaf(h, T[i], one_coef<NB>()) : h * T[i];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i) R[i] = sh.X[b][i][lane];
@@ -111,7 +113,7 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
     const float ec = expf(c);
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      if (group_of<NB>(i) == G) vis[(int64_t)i * P + p] = ec * R[i];
+      if (group_of<NB>(i) == G) vis[(int64_t)i * P + p] = (ec * R[i]) * coef_inv<NB>(i);
   }
 }
 
@@ -159,7 +161,7 @@ __device__ __forceinline__ void taylor_bwd_group(TaylorShared<NB>& sh, int lane,
   __syncthreads();
   float Eb[N], A[N], T[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) Eb[i] = ec * sh.X[1][i][lane];
+  for (int i = 0; i < N; ++i) Eb[i] = (ec * sh.X[1][i][lane]) * cot_scale<NB>(i);
   const float cbar = ((sh.Cb[0][lane] + sh.Cb[1][lane]) + sh.Cb[2][lane]) + sh.Cb[3][lane];
   // Reverse squarings: Ebar_j = 2 (Ebar_{j+1} * E_j).
   for (int j = k - 1; j >= 0; --j) {
@@ -195,7 +197,7 @@ __device__ __forceinline__ void taylor_bwd_group(TaylorShared<NB>& sh, int lane,
       for (int i = 0; i < N; ++i) A[i] = sh.X[0][i][lane];
     } else {
 #pragma unroll
-      for (int i = 0; i < N; ++i) A[i] = i == 0 ? SHV_SQRT_4PI : 0.0f;
+      for (int i = 0; i < N; ++i) A[i] = i == 0 ? one_coef<NB>() : 0.0f;
     }
     const float h = 0.5f / (float)j;
     SqGroup<NB, G>::adj(Eb, A, T);  // group G of 2 (Rb * R_j)
@@ -222,7 +224,7 @@ __device__ __forceinline__ void taylor_bwd_group(TaylorShared<NB>& sh, int lane,
     for (int m = -l; m <= l; ++m) {
       const int i = idx(l, m);
       if (group_of<NB>(i) != G) continue;
-      const float lam = eps * SHV_LAMBDA[l][m < 0 ? -m : m];
+      const float lam = eps * (Lat<NB>::USE ? SHV_LAT_LAMI : SHV_LAMBDA)[l][m < 0 ? -m : m];
       Wout[(int64_t)i * P + p] = i == 0 ? lam * (cbar * SHV_INV_SQRT_4PI) : lam * (scale * Gb[i]);
     }
   }

@@ -1,0 +1,55 @@
+"""Products through latitudes (6 to 8 bands) at the edges of the receiver
+tiles, in every kernel that uses them, against the FP64 oracle.
+
+Tolerances as for the other exponential tests: V ||dV|| / ||V|| <= 1e-5,
+gradients ||d grad|| / ||grad|| <= 1e-4 per parameter group."""
+import numpy as np
+import pytest
+
+import scenegen
+from gpu_helpers import lib, rel_l2, run_hip, run_render
+from oracle import method
+
+pytestmark = pytest.mark.gpu
+
+GRADS = ("grad_points", "grad_normals", "grad_albedo", "grad_spheres", "grad_light")
+
+
+def _check(h, sc, mode="squaring"):
+    o = method.run_forward_backward(sc, sc["grad_radiance"], exp_mode=mode)
+    ev = rel_l2(h["V"], o["V"].numpy())
+    assert ev <= 1e-5, ev
+    for key in GRADS:
+        e = rel_l2(h[key], o[key].numpy())
+        assert e <= 1e-4, (key, e)
+
+
+@pytest.mark.parametrize("n", [6, 7, 8])
+@pytest.mark.parametrize("P", [1, 64, 65, 257])
+def test_tile_edges_in_both_layouts(n, P):
+    L = lib()
+    sc = scenegen.scene_random_shell(600 + n, P, 21, n)
+    four = run_render(sc, sc["grad_radiance"], flags=L.SHV_FLAG_EXP_FOUR_WAVES)
+    _check(four, sc)
+    one = run_render(sc, sc["grad_radiance"], flags=L.SHV_FLAG_EXP_ONE_WAVE)
+    for key in ("V", "B") + GRADS:
+        assert np.array_equal(one[key], four[key]), key
+
+
+@pytest.mark.parametrize("n", [6, 7, 8])
+@pytest.mark.parametrize("mode", ["taylor2", "product"])
+def test_other_modes_at_a_ragged_tile(n, mode):
+    L = lib()
+    flags = L.SHV_FLAG_EXP_PRODUCT if mode == "product" else L.SHV_FLAG_EXP_TAYLOR | L.SHV_FLAG_EXP_TAYLOR_ORDER(2)
+    sc = scenegen.scene_random_shell(700 + n, 65, 21, n)
+    _check(run_hip(sc, sc["grad_radiance"], flags=flags), sc, mode)
+
+
+def test_no_squarings_keep_the_linear_approximation():
+    sc = scenegen.scene_random_shell(808, 65, 5, 8)
+    sc["spheres"][:, 3] *= 0.2        # a small exponent, where k = 0 means something
+    h = run_render(sc, sc["grad_radiance"], k=0)
+    o = method.run_forward_backward(sc, sc["grad_radiance"], n_squarings=0)
+    assert rel_l2(h["V"], o["V"].numpy()) <= 1e-5
+    for key in GRADS:
+        assert rel_l2(h[key], o[key].numpy()) <= 1e-4, key
