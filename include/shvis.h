@@ -78,7 +78,7 @@ typedef int32_t shv_status;
 #define SHV_FLAG_EXP_QUADRATURE 4u /* a different exponential (this flag changes the result): the
                                       projection of the pointwise exponential, V = exp(c) sum_q w_q
                                       exp(Fhat~(w_q)) y(w_q), over the product rule of degree 8n - 1
-                                      (4n Gauss-Legendre nodes in z times 8n azimuths), on MFMA.
+                                      (4n Gauss-Legendre nodes in z times 8n azimuths).
                                       n_squarings is unused.  Only sh_visibility_forward /
                                       sh_visibility_backward accept it; saved then holds F [N][P]. */
 #define SHV_FLAG_EXP_PRODUCT 8u    /* V without logarithms (this flag changes the result): the chain of

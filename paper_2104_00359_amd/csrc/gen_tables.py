@@ -266,33 +266,33 @@ def order_groups(n, ng=N_GROUPS):
     return [sorted(i for i in range(n * n) if grp[abs(lm(i)[1])] == g) for g in range(ng)]
 
 
+def lat_row(n, z, scale):
+    """Entries (m, l), m-major, of scale sqrt(4 pi) N_lm P_l^m(z), N_lm P_l^m
+    being y_lm without its azimuth function (and without the sqrt 2 that has
+    for m > 0), padded to a multiple of four."""
+    out = []
+    r = math.sqrt(1 - z * z)
+    for m in range(n):
+        p = math.sqrt((2 * m + 1) * math.prod((2 * i - 1) / (2 * i) for i in range(1, m + 1))) * r ** m
+        prev, cur = 0.0, p
+        for l in range(m, n):
+            if l > m:
+                a = math.sqrt((4 * l * l - 1) / (l * l - m * m))
+                b = math.sqrt(((l - 1) ** 2 - m * m) / (4 * (l - 1) ** 2 - 1)) if l > m + 1 else 0.0
+                prev, cur = cur, a * (z * cur - b * prev)
+            out.append(scale * cur)
+    return out + [0.0] * (-len(out) % 4)
+
+
 def lat_rows(n):
     """The Gauss-Legendre latitudes z > 0 of the rule that integrates the
     triple products of n bands exactly (degree 3 n - 3), and z = 0 where the
-    rule has it: one row each, entries (m, l) m-major,
-      w^(1/3) sqrt(4 pi) N_lm P_l^m(z),
-    N_lm P_l^m being y_lm without its azimuth function (and without the sqrt 2
-    that has for m > 0).  The transform of each factor and the transposed
-    transform carry w^(1/3) each, so a product carries the weight w = 2 (w / 2):
-    the projection of twice the product."""
+    rule has it: one lat_row each, scaled by w^(1/3).  The transform of each
+    factor and the transposed transform carry w^(1/3) each, so a product
+    carries the weight w = 2 (w / 2): the projection of twice the product."""
     zs, ws = np.polynomial.legendre.leggauss((3 * n - 3) // 2 + 1)
-
-    def row(z, w):
-        out = []
-        r = math.sqrt(1 - z * z)
-        for m in range(n):
-            p = math.sqrt((2 * m + 1) * math.prod((2 * i - 1) / (2 * i) for i in range(1, m + 1))) * r ** m
-            prev, cur = 0.0, p
-            for l in range(m, n):
-                if l > m:
-                    a = math.sqrt((4 * l * l - 1) / (l * l - m * m))
-                    b = math.sqrt(((l - 1) ** 2 - m * m) / (4 * (l - 1) ** 2 - 1)) if l > m + 1 else 0.0
-                    prev, cur = cur, a * (z * cur - b * prev)
-                out.append(w ** (1 / 3) * cur)
-        return out + [0.0] * (-len(out) % 4)
-
-    pairs = [row(z, w) for z, w in zip(zs, ws) if z > 1e-9]
-    eq = [row(0.0, w) for z, w in zip(zs, ws) if abs(z) <= 1e-9]
+    pairs = [lat_row(n, z, w ** (1 / 3)) for z, w in zip(zs, ws) if z > 1e-9]
+    eq = [lat_row(n, 0.0, w ** (1 / 3)) for z, w in zip(zs, ws) if abs(z) <= 1e-9]
     return pairs, eq
 
 
@@ -321,6 +321,31 @@ def emit_lat(L):
                 for i in members:
                     gid[i] = g
             L.append(f"static constexpr unsigned char {name}_{n}[{n * n}] = {{" + ",".join(map(str, gid)) + "};")
+
+
+def emit_quad(L):
+    """The product rule of degree 8 n - 1: 4 n Gauss-Legendre latitudes, as
+    the rows and weights of the pairs +-z, and 8 n azimuths (j + 1/2) 2 pi / 8 n,
+    as the cosines and sines of m phi_j in the first quarter."""
+    L.append("// Quadrature of the projected exponential (shv_quad_impl.h).")
+    lamb = recurrence_constants()[1]
+    for n in range(1, MAX_BANDS + 1):
+        zs, ws = np.polynomial.legendre.leggauss(4 * n)
+        up = [(z, w) for z, w in zip(zs, ws) if z > 0]
+        rows = [v for z, _ in up for v in lat_row(n, z, 1.0)]
+        L.append(f"static constexpr float shv_quad_rows_{n}[{len(rows)}] = {{" + ",".join(flit(v) for v in rows) + "};")
+        # the weight of each of the latitude's azimuths
+        L.append(f"static constexpr float shv_quad_w_{n}[{len(up)}] = {{"
+                 + ",".join(flit(w * 2 * PI / (8 * n)) for _, w in up) + "};")
+        for name, f in (("cos", math.cos), ("sin", math.sin)):
+            L.append(f"static constexpr float shv_quad_{name}_{n}[{2 * n}][{n}] = {{" + ",".join(
+                "{" + ",".join(flit(f(m * (j + 0.5) * 2 * PI / (8 * n))) for m in range(n)) + "}"
+                for j in range(2 * n)) + "};")
+    for name, f in (("norm", lambda l, m: (1.0 if m == 0 else math.sqrt(2.0)) / math.sqrt(4 * PI)),
+                    ("lam", lambda l, m: lamb[l][abs(m)])):
+        L.append(f"// {'y_lm over its row entry' if name == 'norm' else 'LAMBDA[l][|m|]'}, by coefficient index.")
+        L.append(f"static constexpr float shv_coef_{name}[{MAX_BANDS ** 2}] = {{"
+                 + ",".join(flit(f(*lm(i))) for i in range(MAX_BANDS ** 2)) + "};")
 
 
 # ----------------------------------------------------------------- emission
@@ -549,12 +574,7 @@ def emit_gaunt(path):
         L.append(f"__device__ const unsigned short shv_ltab_pent_{n}[{len(pent)}] = {{" + ",".join(map(str, pent)) + "};")
         L.append(f"__device__ const float shv_ltab_pval_{n}[{len(pval)}] = {{" + ",".join(flit(c) for c in pval) + "};")
     L.append("")
-    L.append("// Quadrature of the projected exponential: Gauss-Legendre nodes and weights in z,")
-    L.append("// 4n of them for n bands (the rule of degree 8n - 1 with 8n uniform azimuths).")
-    for n in range(1, MAX_BANDS + 1):
-        z, wz = np.polynomial.legendre.leggauss(4 * n)
-        L.append(f"__device__ const float shv_quad_z_{n}[{4 * n}] = {{" + ",".join(flit(v) for v in z) + "};")
-        L.append(f"__device__ const float shv_quad_w_{n}[{4 * n}] = {{" + ",".join(flit(v) for v in wz) + "};")
+    emit_quad(L)
     L.append("")
     emit_lat(L)
     L.append("")

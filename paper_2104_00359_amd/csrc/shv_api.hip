@@ -195,13 +195,6 @@ size_t fwd_bytes(int64_t P, int64_t S, int nb, FwdWs* o = nullptr) {
   if (o) o->fpart = 0;
   return fpart;
 }
-// The quadrature exponential's basis table and partial sums (after the
-// phase's own workspace).
-size_t quad_table_bytes(int nb) { return align_up((size_t)shv::quad_table_floats(nb) * 4); }
-size_t quad_bytes(int nb, int64_t P) {
-  return quad_table_bytes(nb) + align_up((size_t)shv::quad_part_floats(nb, P) * 4);
-}
-
 // The direct product chain's adjoint: every step's input [S][N][P] and the
 // sphere-gradient partials, one row per (block, wave).
 struct ProdWs {
@@ -444,10 +437,6 @@ size_t shv_workspace_bytes(int64_t P, int64_t S, const shv_params* prm) {
   b = std::max(b, visbwd_bytes(P, S, nb));
   b = std::max(b, render_fwd_bytes(P, S, nb));
   b = std::max(b, render_bwd_bytes(P, S, nb));
-  if (prm->flags & SHV_FLAG_EXP_QUADRATURE) {
-    b = std::max(b, fwd_bytes(P, S, nb) + quad_bytes(nb, P));
-    b = std::max(b, visbwd_bytes(P, S, nb) + quad_bytes(nb, P));
-  }
   if (prm->flags & SHV_FLAG_EXP_PRODUCT) b = std::max(b, prod_bytes(P, S, nb));
   return b;
 }
@@ -601,8 +590,7 @@ shv_status sh_visibility_forward(const float* points, int64_t P, const float* sp
     }));
     return SHV_OK;
   }
-  const size_t base = fwd_bytes(P, S, nb);
-  SHV_TRY(check_ws(ws, ws_bytes, base + (quadrature(prm) ? quad_bytes(nb, P) : 0)));
+  SHV_TRY(check_ws(ws, ws_bytes, fwd_bytes(P, S, nb)));
   SHV_TRY(check_device());
   float* Fpart = (float*)ws;
   const shv::Split sp = shv::fwd_split(P, S);
@@ -611,8 +599,7 @@ shv_status sh_visibility_forward(const float* points, int64_t P, const float* sp
   }));
   if (quadrature(prm)) {
     SHV_TRY(launch("exp_quad_fwd", stream, [&] {
-      return shv::launch_exp_quad_fwd(nb, Fpart, sp.nchunks, P, prm->eps, vis, saved, (float*)((char*)ws + base),
-                                      (float*)((char*)ws + base + quad_table_bytes(nb)), stream);
+      return shv::launch_exp_quad_fwd(nb, Fpart, sp.nchunks, P, prm->eps, vis, saved, stream);
     }));
     return SHV_OK;
   }
@@ -996,8 +983,7 @@ shv_status sh_visibility_backward(const float* grad_vis, const float* vis, const
     return SHV_OK;
   }
   VisBwdWs L;
-  const size_t base = visbwd_bytes(P, S, nb, &L);
-  SHV_TRY(check_ws(ws, ws_bytes, base + (quadrature(prm) ? quad_bytes(nb, P) : 0)));
+  SHV_TRY(check_ws(ws, ws_bytes, visbwd_bytes(P, S, nb, &L)));
   SHV_TRY(check_device());
   float* W = (float*)((char*)ws + L.W);
   float* gp = (float*)((char*)ws + L.gp);
@@ -1005,8 +991,7 @@ shv_status sh_visibility_backward(const float* grad_vis, const float* vis, const
   const shv::Split sp = shv::bwd_split(P, S);
   if (quadrature(prm)) {
     SHV_TRY(launch("exp_quad_bwd", stream, [&] {
-      return shv::launch_exp_quad_bwd(nb, grad_vis, vis, saved, P, prm->eps, W, (float*)((char*)ws + base),
-                                      (float*)((char*)ws + base + quad_table_bytes(nb)), stream);
+      return shv::launch_exp_quad_bwd(nb, grad_vis, vis, saved, P, prm->eps, W, stream);
     }));
   } else if (taylor(prm)) {
     SHV_TRY(launch("exp_taylor_bwd", stream, [&] {

@@ -47,10 +47,9 @@ template hipError_t batch_exp_fwd_nb<SHV_NB>(const void*, bool, int64_t, hipStre
 #elif SHV_PART == 5
 template hipError_t batch_exp_bwd_nb<SHV_NB>(const void*, bool, int64_t, hipStream_t);
 #elif SHV_PART == 6
-template hipError_t exp_quad_fwd_nb<SHV_NB>(const float*, int, int64_t, float, float*, float*, float*, float*,
+template hipError_t exp_quad_fwd_nb<SHV_NB>(const float*, int, int64_t, float, float*, float*, hipStream_t);
+template hipError_t exp_quad_bwd_nb<SHV_NB>(const float*, const float*, const float*, int64_t, float, float*,
                                             hipStream_t);
-template hipError_t exp_quad_bwd_nb<SHV_NB>(const float*, const float*, const float*, int64_t, float, float*, float*,
-                                            float*, hipStream_t);
 #elif SHV_PART == 7
 template hipError_t prod_fwd_nb<SHV_NB>(const float*, int64_t, const float*, int, float, float*, float*, hipStream_t);
 template hipError_t prod_bwd_nb<SHV_NB>(const float*, const float*, const float*, int64_t, const float*, int, float,

@@ -1,42 +1,50 @@
 // The SH exponential as the projection of the pointwise exponential (the
 // function-space quantity that the scaling and squaring scheme stands in for),
-// taken with a fixed quadrature on MFMA.  A selectable accuracy mode; it
-// changes the result.
+// taken with a fixed quadrature.  A selectable accuracy mode; it changes the
+// result.
 //
 //   F = eps * lambda * (sum of the sphere-chunk partials)   (as in the squaring path)
 //   c = F_0 / sqrt(4 pi),  f_q = sum_{i >= 1} F_i y_i(w_q)
 //   V = exp(c) sum_q w_q exp(f_q) y(w_q)
-// over the product rule of degree 8n - 1: 4n Gauss-Legendre nodes in z times
-// 8n uniform azimuths (weights wz * 2 pi / 8n), padded to a multiple of 64
-// nodes with zero weights.
+// over the product rule of degree 8n - 1: 4n Gauss-Legendre latitudes times 8n
+// azimuths (j + 1/2) 2 pi / 8n.
 //
-// For a block of 64 receivers and a tile of 64 nodes the two sums are GEMMs:
-//   f [64 rec x 64 nodes] = Fhat [64 x 64 coef] * Y [64 coef x 64 nodes]
-//   V [64 rec x 64 coef] += (w exp f) [64 x 64 nodes] * Y^T [64 nodes x 64 coef]
-// (coefficients padded to 64).  Four waves each own one 32 x 32 quadrant of
-// both and run them on v_mfma_f32_32x32x2f32; the tile's Y is evaluated in LDS
-// from the node directions, and w exp f goes through LDS between the GEMMs.
+// The sums over the nodes are separable.  Per latitude, f's Fourier
+// coefficients come from a Legendre transform; an azimuth in the first quarter gives f at its four
+// mirror images from four short sums (cosines and sines of even and odd order);
+// the exponentials go back through the same two steps transposed.  At 8 bands
+// and 2,048 nodes that is about 34,000 instructions per receiver, exponentials
+// included, where the sums as dense products with the nodes' basis were 262,000
+// multiply-adds on MFMA.
 //
 // Adjoint for Vbar: Fbar_0 = (sum_j Vbar_j V_j) / sqrt(4 pi) and, for i >= 1,
-//   Fbar_i = exp(c) sum_q w_q exp(f_q) g_q y_i(w_q),  g_q = sum_j Vbar_j y_j(w_q)
-// (three GEMMs per tile); W = eps * lambda * Fbar feeds the pair adjoint.
+//   Fbar_i = exp(c) sum_q w_q exp(f_q) g_q y_i(w_q),  g_q = sum_j Vbar_j y_j(w_q),
+// g by the same two steps as f; W = eps * lambda * Fbar feeds the pair adjoint.
+//
+// Layout: one receiver per lane, the latitudes dealt to the eight waves of a
+// block (four at 1 band), whose partial sums are added in wave order through
+// LDS at the end.  F (and Vbar) stay in LDS for all waves, so that a wave's
+// registers hold one latitude's coefficients and its 64 sums: 128 registers,
+// four waves per SIMD, and two blocks fit a CU.  Bound by
+// VALU issue, with 57 of the CUs holding two of the 313 blocks at 20,000
+// receivers.  Measured there at 8 bands: forward 159 -> 33 us, adjoint 196 -> 45
+// us, and the launches that built the nodes' basis and added partial sums (21
+// us) are gone.
 #pragma once
 
 #include "shv_exp_impl.h"
 
 namespace shv {
 
-typedef float mfma_f32x16 __attribute__((ext_vector_type(16)));
-
-constexpr int kQuadPitch = 65;  // LDS row pitch of the 64 x 64 tiles (no bank conflicts down a column)
-
 template <int NB>
 struct QuadTab;
-#define SHV_QTAB(n)                                                                         \
-  template <>                                                                               \
-  struct QuadTab<n> {                                                                       \
-    static __device__ __forceinline__ float z(int i) { return shv_quad_z_##n[i]; }          \
-    static __device__ __forceinline__ float w(int i) { return shv_quad_w_##n[i]; }          \
+#define SHV_QTAB(n)                                                                                       \
+  template <>                                                                                             \
+  struct QuadTab<n> {                                                                                     \
+    static __device__ __forceinline__ const float* rows() { return shv_quad_rows_##n; }                   \
+    static __device__ __forceinline__ float w(int t) { return shv_quad_w_##n[t]; }                        \
+    static __device__ __forceinline__ constexpr float cosm(int j, int m) { return shv_quad_cos_##n[j][m]; } \
+    static __device__ __forceinline__ constexpr float sinm(int j, int m) { return shv_quad_sin_##n[j][m]; } \
   };
 SHV_QTAB(1)
 SHV_QTAB(2)
@@ -49,284 +57,239 @@ SHV_QTAB(8)
 #undef SHV_QTAB
 
 template <int NB>
-struct QuadRule {
-  static constexpr int NZ = 4 * NB;           // Gauss-Legendre nodes in z
-  static constexpr int NPHI = 8 * NB;         // uniform azimuths
-  static constexpr int Q = NZ * NPHI;         // real nodes
-  static constexpr int QP = (Q + 63) / 64 * 64;
+struct Quad {
+  static constexpr int N = NB * NB;
+  static constexpr int LATS = 4 * NB;                     // latitudes
+  static constexpr int QUARTER = 2 * NB;                  // azimuths in a quarter
+  static constexpr int WAVES = LATS < 8 ? LATS : 8;       // per block of 64 receivers
+  static constexpr int H = (N + 1) / 2;                   // coefficients per exchange of the waves' sums
 };
 
-// Node q of the rule: direction and weight (weight 0 for the padding nodes).
-template <int NB>
-__device__ __forceinline__ void quad_node(int q, float& x, float& y, float& z, float& w) {
-  constexpr int NPHI = QuadRule<NB>::NPHI;
-  if (q >= QuadRule<NB>::Q) {
-    x = 0.0f;
-    y = 0.0f;
-    z = 1.0f;
-    w = 0.0f;
-    return;
-  }
-  const int zi = q / NPHI, mi = q - zi * NPHI;
-  z = QuadTab<NB>::z(zi);
-  const float st = sqrtf(fmaxf(0.0f, 1.0f - z * z));
-  float s, c;
-  sincosf(((float)mi + 0.5f) * (SHV_TWO_PI / (float)NPHI), &s, &c);
-  x = st * c;
-  y = st * s;
-  w = QuadTab<NB>::w(zi) * (SHV_TWO_PI / (float)NPHI);
-}
-
+template <int NB, bool ADJ>
 struct QuadShared {
-  float Yt[64 * kQuadPitch];  // Yt[coef * pitch + node]
-  float Et[64 * kQuadPitch];  // Et[rec * pitch + node]
-  float wq[64];
-  float cs[64];               // c of each receiver
+  union {
+    struct {
+      float F[NB * NB][64];            // scaled so that a row's entries give Fourier amplitudes of log2(e) f
+      float G[ADJ ? NB * NB : 1][64];  // Vbar, likewise for g
+    } in;
+    float red[Quad<NB>::WAVES][Quad<NB>::H][64];
+  };
+  float c[64];
+  float cb[Quad<NB>::WAVES][64];  // partial sums of Vbar . V
 };
 
-// The rule's basis table: Ytab[q * 64 + t] = y_t(w_q) (0 for t >= N) and
-// wtab[q], one thread per node (once per call; every block then reads it).
-template <int NB>
-__global__ __launch_bounds__(SHV_BLOCK) void k_quad_table(float* __restrict__ Ytab, float* __restrict__ wtab) {
-  constexpr int N = NB * NB;
-  const int q = blockIdx.x * SHV_BLOCK + threadIdx.x;
-  if (q >= QuadRule<NB>::QP) return;
-  float x, y, z, w;
-  quad_node<NB>(q, x, y, z, w);
-  float Y[N];
-  sh_eval<NB>(x, y, z, Y);
+// Fourier amplitudes at sgn z of the function with coefficients e (in LDS).
+template <int NB, bool MEAN>
+__device__ __forceinline__ void quad_up(const float (*e)[64], int lane, const float* __restrict__ Q, float sgn,
+                                        float (&A)[NB], float (&B)[NB]) {
 #pragma unroll
-  for (int t = 0; t < 64; ++t) Ytab[(int64_t)q * 64 + t] = t < N ? Y[t < N ? t : 0] : 0.0f;
-  wtab[q] = w;
-}
-
-// The tile's 64 nodes from the table into Yt [coef][node] and wq: thread t
-// copies 16 coefficients (t % 4) of node t / 4 (float4 loads).
-__device__ __forceinline__ void quad_tile_load(QuadShared& sh, const float* __restrict__ Ytab,
-                                               const float* __restrict__ wtab, int q0) {
-  const int node = threadIdx.x >> 2, part = threadIdx.x & 3;
-  const float4* src = reinterpret_cast<const float4*>(Ytab + (int64_t)(q0 + node) * 64 + 16 * part);
+  for (int m = 0; m < NB; ++m) {
+    float a[2] = {0.0f, 0.0f}, b[2] = {0.0f, 0.0f};  // even and odd l - m
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const float4 y = src[v];
-    const int c = 16 * part + 4 * v;
-    sh.Yt[(c + 0) * kQuadPitch + node] = y.x;
-    sh.Yt[(c + 1) * kQuadPitch + node] = y.y;
-    sh.Yt[(c + 2) * kQuadPitch + node] = y.z;
-    sh.Yt[(c + 3) * kQuadPitch + node] = y.w;
-  }
-  if (part == 0) sh.wq[node] = wtab[q0 + node];
-}
-
-// 32 x 32 quadrant (rows ra.., cols cb..) of A [64 x 64 K] * B [64 K x 64]
-// with A taken from the lane's registers a[32] (A[ra + l % 32][2s + l / 32])
-// and B from LDS as Bsrc[(2s + l / 32) * bk + (cb + l % 32) * bn].
-__device__ __forceinline__ mfma_f32x16 quad_gemm_regA(const float (&a)[32], const float* Bsrc, int bk, int bn,
-                                                     int cb, mfma_f32x16 acc) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int s = 0; s < 32; ++s) {
-    const float b = Bsrc[(2 * s + (lane >> 5)) * bk + (cb + (lane & 31)) * bn];
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-// Both operands from LDS: A as Asrc[(ra + l % 32) * ak + (2s + l / 32)].
-__device__ __forceinline__ mfma_f32x16 quad_gemm_lds(const float* Asrc, int ak, int ra, const float* Bsrc, int bk,
-                                                    int bn, int cb, mfma_f32x16 acc) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll 8
-  for (int s = 0; s < 32; ++s) {
-    const float a = Asrc[(ra + (lane & 31)) * ak + 2 * s + (lane >> 5)];
-    const float b = Bsrc[(2 * s + (lane >> 5)) * bk + (cb + (lane & 31)) * bn];
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-// Row (within the 32 x 32 quadrant) of accumulator element r of this lane.
-__device__ __forceinline__ int quad_row(int r) { return 8 * (r >> 2) + 4 * ((threadIdx.x & 63) >> 5) + (r & 3); }
-
-// The lane's A operand rows of F-like data: a[s] = X[coef 2s + l / 32][rec ra + l % 32]
-// for a row-major [N][P] array (0 past N or P), summed over `chunks` arrays `stride` apart.
-template <int NB>
-__device__ __forceinline__ void quad_load_rows(const float* __restrict__ X, int chunks, int64_t stride, int64_t P,
-                                               int64_t p, bool ok, float (&a)[32]) {
-  constexpr int N = NB * NB;
-  const int half = (threadIdx.x & 63) >> 5;
-  const int64_t q = ok ? p : 0;
-  // Chunk by chunk, each chunk's 32 loads issued together (the sum per row
-  // is still taken in chunk order).
-#pragma unroll
-  for (int s = 0; s < 32; ++s) {
-    const int coef = 2 * s + half;
-    a[s] = X[(int64_t)(coef < N ? coef : N - 1) * P + q];
-  }
-  for (int c = 1; c < chunks; ++c) {
-    const float* src = X + c * stride + q;
-    float t[32];
-#pragma unroll
-    for (int s = 0; s < 32; ++s) {
-      const int coef = 2 * s + half;
-      t[s] = src[(int64_t)(coef < N ? coef : N - 1) * P];
+    for (int l = m; l < NB; ++l) {
+      if (l == 0 && !MEAN) continue;
+      const int s = (l - m) & 1;
+      const float t = Q[lat_at<NB>(m) + l - m];
+      a[s] = fmaf(t, e[idx(l, m)][lane], a[s]);
+      if (m > 0) b[s] = fmaf(t, e[idx(l, -m)][lane], b[s]);
     }
-#pragma unroll
-    for (int s = 0; s < 32; ++s) a[s] += t[s];
-  }
-#pragma unroll
-  for (int s = 0; s < 32; ++s) a[s] = (ok && 2 * s + half < N) ? a[s] : 0.0f;
-}
-
-// Forward: Fpart [nchunks][N][P] -> vis [gridDim.y][N][P], the partial sums of
-// V over the node tiles y, y + gridDim.y, ... (added afterwards in order);
-// saved (may be NULL) <- F [N][P].
-template <int NB>
-__global__ __launch_bounds__(SHV_BLOCK) void k_exp_quad_fwd(const float* __restrict__ Fpart, int nchunks, int64_t P,
-                                                            float eps, float* __restrict__ vis,
-                                                            float* __restrict__ saved,
-                                                            const float* __restrict__ Ytab,
-                                                            const float* __restrict__ wtab) {
-  constexpr int N = NB * NB;
-  __shared__ QuadShared sh;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ra = 32 * (wave & 1), cb = 32 * (wave >> 1);
-  const int half = lane >> 5;
-  const int64_t p = (int64_t)blockIdx.x * 64 + ra + (lane & 31);
-  const bool ok = p < P;
-  float a[32];
-  quad_load_rows<NB>(Fpart, nchunks, (int64_t)N * P, P, p, ok, a);
-#pragma unroll
-  for (int s = 0; s < 32; ++s) a[s] *= eps * coef_lambda(2 * s + half < N ? 2 * s + half : 0);
-  if (cb == 0 && ok && saved && blockIdx.y == 0) {
-#pragma unroll
-    for (int s = 0; s < 32; ++s)
-      if (2 * s + half < N) saved[(int64_t)(2 * s + half) * P + p] = a[s];
-  }
-  if (cb == 0 && half == 0) sh.cs[ra + (lane & 31)] = a[0] * SHV_INV_SQRT_4PI;
-  if (half == 0) a[0] = 0.0f;  // the DC term is split off exactly
-  mfma_f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-  for (int q0 = 64 * blockIdx.y; q0 < QuadRule<NB>::QP; q0 += 64 * gridDim.y) {
-    quad_tile_load(sh, Ytab, wtab, q0);
-    __syncthreads();
-    mfma_f32x16 f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) f[r] = 0.0f;
-    f = quad_gemm_regA(a, sh.Yt, kQuadPitch, 1, cb, f);  // rows: receivers ra.., cols: nodes cb..
-    const float w = sh.wq[cb + (lane & 31)];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sh.Et[(ra + quad_row(r)) * kQuadPitch + cb + (lane & 31)] = w * expf(f[r]);
-    __syncthreads();
-    // rows: receivers ra.., cols: coefficients cb.., K: the tile's nodes
-    acc = quad_gemm_lds(sh.Et, kQuadPitch, ra, sh.Yt, 1, kQuadPitch, cb, acc);
-    __syncthreads();
-  }
-  const int coef = cb + (lane & 31);
-  if (coef >= N) return;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int rec = ra + quad_row(r);
-    const int64_t pr = (int64_t)blockIdx.x * 64 + rec;
-    if (pr < P) vis[blockIdx.y * (int64_t)N * P + (int64_t)coef * P + pr] = expf(sh.cs[rec]) * acc[r];
+    A[m] = fmaf(sgn, a[1], a[0]);
+    B[m] = fmaf(sgn, b[1], b[0]);
   }
 }
 
-// Adjoint: gV, vis, saved F [N][P] -> W [gridDim.y][N][P], partial sums of
-// eps lambda Fbar over the node tiles as in the forward.
+// Values at azimuths phi, -phi, pi - phi, pi + phi, phi the quarter's j-th.
 template <int NB>
-__global__ __launch_bounds__(SHV_BLOCK) void k_exp_quad_bwd(const float* __restrict__ gV,
-                                                            const float* __restrict__ vis,
-                                                            const float* __restrict__ saved, int64_t P, float eps,
-                                                            float* __restrict__ W, const float* __restrict__ Ytab,
-                                                            const float* __restrict__ wtab) {
-  constexpr int N = NB * NB;
-  __shared__ QuadShared sh;
-  __shared__ float cbar[64];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ra = 32 * (wave & 1), cb = 32 * (wave >> 1);
-  const int half = lane >> 5;
-  const int64_t p = (int64_t)blockIdx.x * 64 + ra + (lane & 31);
-  const bool ok = p < P;
-  float a[32], g[32];
-  quad_load_rows<NB>(saved, 1, 0, P, p, ok, a);
-  quad_load_rows<NB>(gV, 1, 0, P, p, ok, g);
-  if (cb == 0 && half == 0) sh.cs[ra + (lane & 31)] = a[0] * SHV_INV_SQRT_4PI;
-  if (half == 0) a[0] = 0.0f;
-  if (threadIdx.x < 64) {  // sum_j Vbar_j V_j per receiver, j in index order
-    const int64_t pr = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    const int64_t q = pr < P ? pr : 0;
-    float s = 0.0f;
+__device__ __forceinline__ void quad_values(const float (&A)[NB], const float (&B)[NB], int j, float (&f)[4]) {
+  float ce = A[0], co = 0.0f, se = 0.0f, so = 0.0f;  // cosines and sines of even and odd order
 #pragma unroll
-    for (int j = 0; j < N; ++j) s = fmaf(gV[(int64_t)j * P + q], vis[(int64_t)j * P + q], s);
-    cbar[threadIdx.x] = pr < P ? s : 0.0f;
-  }
-  mfma_f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-  for (int q0 = 64 * blockIdx.y; q0 < QuadRule<NB>::QP; q0 += 64 * gridDim.y) {
-    quad_tile_load(sh, Ytab, wtab, q0);
-    __syncthreads();
-    mfma_f32x16 f, gq;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      f[r] = 0.0f;
-      gq[r] = 0.0f;
+  for (int m = 1; m < NB; ++m) {
+    const float c = QuadTab<NB>::cosm(j, m), s = QuadTab<NB>::sinm(j, m);
+    if (m & 1) {
+      co = m == 1 ? c * A[m] : fmaf(c, A[m], co);
+      so = m == 1 ? s * B[m] : fmaf(s, B[m], so);
+    } else {
+      ce = fmaf(c, A[m], ce);
+      se = m == 2 ? s * B[m] : fmaf(s, B[m], se);
     }
-    f = quad_gemm_regA(a, sh.Yt, kQuadPitch, 1, cb, f);
-    gq = quad_gemm_regA(g, sh.Yt, kQuadPitch, 1, cb, gq);
-    const float w = sh.wq[cb + (lane & 31)];
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      sh.Et[(ra + quad_row(r)) * kQuadPitch + cb + (lane & 31)] = w * expf(f[r]) * gq[r];
-    __syncthreads();
-    acc = quad_gemm_lds(sh.Et, kQuadPitch, ra, sh.Yt, 1, kQuadPitch, cb, acc);
-    __syncthreads();
   }
-  const int coef = cb + (lane & 31);
-  if (coef >= N) return;
-  const float lam = eps * coef_lambda(coef);
+  const float p = ce + co, q = so + se, r = ce - co, t = so - se;
+  f[0] = p + q;
+  f[1] = p - q;
+  f[2] = r + t;
+  f[3] = r - t;
+}
+
+// The transposed step: C_m += sum of cos(m phi) v, S_m += sum of sin(m phi) v over the four.
+template <int NB>
+__device__ __forceinline__ void quad_gather(const float (&v)[4], int j, float (&C)[NB], float (&S)[NB]) {
+  const float p = v[0] + v[1], q = v[2] + v[3], r = v[0] - v[1], t = v[2] - v[3];
+  const float ce = p + q, co = p - q, so = r + t, se = r - t;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int rec = ra + quad_row(r);
-    const int64_t pr = (int64_t)blockIdx.x * 64 + rec;
-    if (pr >= P) continue;
-    const float fb = coef == 0 ? (blockIdx.y == 0 ? cbar[rec] * SHV_INV_SQRT_4PI : 0.0f) : expf(sh.cs[rec]) * acc[r];
-    W[blockIdx.y * (int64_t)N * P + (int64_t)coef * P + pr] = lam * fb;
+  for (int m = 0; m < NB; ++m) {
+    if (m == 0) {
+      C[0] += ce;
+      continue;
+    }
+    C[m] = fmaf(QuadTab<NB>::cosm(j, m), (m & 1) ? co : ce, C[m]);
+    S[m] = fmaf(QuadTab<NB>::sinm(j, m), (m & 1) ? so : se, S[m]);
   }
 }
 
-// table: QuadRule<NB>::QP * 65 floats (the basis, then the weights); part:
-// kQuadSplits * N * P floats, the per-split partial sums added in split order.
-constexpr int kQuadSplits = 2;  // blocks per 64-receiver tile (node tiles interleaved)
+// acc += the transposed transform of one latitude's sums, times the nodes' weight.
+template <int NB>
+__device__ __forceinline__ void quad_down(const float* __restrict__ Q, float sgn, float w, const float (&C)[NB],
+                                          const float (&S)[NB], float (&acc)[NB * NB]) {
+#pragma unroll
+  for (int m = 0; m < NB; ++m) {
+    const float ea = w * C[m], eb = w * S[m], oa = sgn * ea, ob = sgn * eb;
+#pragma unroll
+    for (int l = m; l < NB; ++l) {
+      const float t = Q[lat_at<NB>(m) + l - m];
+      const bool odd = ((l - m) & 1) != 0;
+      acc[idx(l, m)] = fmaf(t, odd ? oa : ea, acc[idx(l, m)]);
+      if (m > 0) acc[idx(l, -m)] = fmaf(t, odd ? ob : eb, acc[idx(l, -m)]);
+    }
+  }
+}
+
+// This wave's latitudes: acc = sum over their nodes of w exp(f) (ADJ: times g) times the rows.
+template <int NB, bool ADJ>
+__device__ __forceinline__ void quad_sums(const QuadShared<NB, ADJ>& sh, int wave, int lane, float (&acc)[NB * NB]) {
+#pragma unroll
+  for (int i = 0; i < NB * NB; ++i) acc[i] = 0.0f;
+#pragma unroll 1
+  for (int t = wave; t < Quad<NB>::LATS; t += Quad<NB>::WAVES) {
+    asm volatile("" ::: "memory");  // F and Vbar are read again per latitude rather than held in registers
+    const float* __restrict__ Q = QuadTab<NB>::rows() + (t >> 1) * Lat<NB>::QP;
+    const float sgn = (t & 1) ? -1.0f : 1.0f;
+    float A[NB], B[NB], X[NB], Y[NB], C[NB], S[NB];
+    quad_up<NB, false>(sh.in.F, lane, Q, sgn, A, B);
+    if constexpr (ADJ) quad_up<NB, true>(sh.in.G, lane, Q, sgn, X, Y);
+#pragma unroll
+    for (int m = 0; m < NB; ++m) C[m] = S[m] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < Quad<NB>::QUARTER; ++j) {
+      float f[4];
+      quad_values<NB>(A, B, j, f);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) f[x] = __builtin_amdgcn_exp2f(f[x]);
+      if constexpr (ADJ) {
+        float g[4];
+        quad_values<NB>(X, Y, j, g);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) f[x] *= g[x];
+      }
+      quad_gather<NB>(f, j, C, S);
+    }
+    quad_down<NB>(Q, sgn, QuadTab<NB>::w(t >> 1), C, S, acc);
+  }
+}
+
+// The waves' sums added in wave order, half of the coefficients at a time;
+// wave w hands rows w, w + WAVES, ... of a half to put(i, sum).
+template <int NB, bool ADJ, class Put>
+__device__ __forceinline__ void quad_reduce(QuadShared<NB, ADJ>& sh, int wave, int lane, const float (&acc)[NB * NB],
+                                            Put put) {
+  constexpr int N = NB * NB, H = Quad<NB>::H, W = Quad<NB>::WAVES;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    __syncthreads();  // the inputs (h = 0) or the first half's sums (h = 1) have been read
+#pragma unroll
+    for (int i = h * H; i < N && i < (h + 1) * H; ++i) sh.red[wave][i - h * H][lane] = acc[i];
+    __syncthreads();
+    for (int i = h * H + wave; i < N && i < (h + 1) * H; i += W) {
+      float v = sh.red[0][i - h * H][lane];
+#pragma unroll
+      for (int w = 1; w < W; ++w) v += sh.red[w][i - h * H][lane];
+      put(i, v);
+    }
+  }
+}
+
+constexpr float kLog2e = 1.44269504088896341f;
+
+// Forward: Fpart [nchunks][N][P] -> vis [N][P]; saved (may be NULL) <- F [N][P].
+template <int NB>
+__global__ __launch_bounds__(64 * Quad<NB>::WAVES, 4) void k_exp_quad_fwd(const float* __restrict__ Fpart, int nchunks,
+                                                                          int64_t P, float eps,
+                                                                          float* __restrict__ vis,
+                                                                          float* __restrict__ saved) {
+  constexpr int N = NB * NB, W = Quad<NB>::WAVES;
+  __shared__ QuadShared<NB, false> sh;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t p = (int64_t)blockIdx.x * 64 + lane;
+  const bool ok = p < P;
+  const int64_t q = ok ? p : 0;  // valid receiver for the loads of tail lanes
+#pragma unroll 4
+  for (int i = wave; i < N; i += W) {
+    float v = Fpart[(int64_t)i * P + q];
+    for (int c = 1; c < nchunks; ++c) v += Fpart[((int64_t)c * N + i) * P + q];
+    v *= eps * shv_coef_lam[i];
+    if (saved && ok) saved[(int64_t)i * P + p] = v;
+    if (i == 0) sh.c[lane] = v * SHV_INV_SQRT_4PI;
+    sh.in.F[i][lane] = v * (shv_coef_norm[i] * kLog2e);
+  }
+  __syncthreads();
+  float acc[N];
+  quad_sums<NB, false>(sh, wave, lane, acc);
+  const float ec = expf(sh.c[lane]);
+  quad_reduce<NB, false>(sh, wave, lane, acc, [&](int i, float v) {
+    if (ok) vis[(int64_t)i * P + p] = ec * (shv_coef_norm[i] * v);
+  });
+}
+
+// Adjoint: gV, vis, saved F [N][P] -> W = eps lambda Fbar [N][P].
+template <int NB>
+__global__ __launch_bounds__(64 * Quad<NB>::WAVES, 4) void k_exp_quad_bwd(const float* __restrict__ gV,
+                                                                          const float* __restrict__ vis,
+                                                                          const float* __restrict__ saved, int64_t P,
+                                                                          float eps, float* __restrict__ Wout) {
+  constexpr int N = NB * NB, W = Quad<NB>::WAVES;
+  __shared__ QuadShared<NB, true> sh;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t p = (int64_t)blockIdx.x * 64 + lane;
+  const bool ok = p < P;
+  const int64_t q = ok ? p : 0;  // valid receiver for the loads of tail lanes
+  float part = 0.0f;
+#pragma unroll 4
+  for (int i = wave; i < N; i += W) {
+    const float f = saved[(int64_t)i * P + q], g = gV[(int64_t)i * P + q];
+    part = fmaf(g, vis[(int64_t)i * P + q], part);
+    if (i == 0) sh.c[lane] = f * SHV_INV_SQRT_4PI;
+    sh.in.F[i][lane] = f * (shv_coef_norm[i] * kLog2e);
+    sh.in.G[i][lane] = g * shv_coef_norm[i];
+  }
+  sh.cb[wave][lane] = part;
+  __syncthreads();
+  float acc[N];
+  quad_sums<NB, true>(sh, wave, lane, acc);
+  const float ec = expf(sh.c[lane]);
+  quad_reduce<NB, true>(sh, wave, lane, acc, [&](int i, float v) {
+    if (!ok) return;
+    float fb = ec * (shv_coef_norm[i] * v);
+    if (i == 0) {
+      float cbar = sh.cb[0][lane];
+#pragma unroll
+      for (int w = 1; w < W; ++w) cbar += sh.cb[w][lane];
+      fb = cbar * SHV_INV_SQRT_4PI;
+    }
+    Wout[(int64_t)i * P + p] = eps * shv_coef_lam[i] * fb;
+  });
+}
 
 template <int NB>
 hipError_t exp_quad_fwd_nb(const float* Fpart, int nchunks, int64_t P, float eps, float* vis, float* saved,
-                           float* table, float* part, hipStream_t st) {
-  constexpr int QP = QuadRule<NB>::QP, N = NB * NB;
-  float* Ytab = table;
-  float* wtab = table + (int64_t)QP * 64;
-  k_quad_table<NB><<<(QP + SHV_BLOCK - 1) / SHV_BLOCK, SHV_BLOCK, 0, st>>>(Ytab, wtab);
-  k_exp_quad_fwd<NB><<<dim3((unsigned)pair_blocks(P), kQuadSplits), SHV_BLOCK, 0, st>>>(Fpart, nchunks, P, eps, part,
-                                                                                        saved, Ytab, wtab);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_sum_chunks(part, kQuadSplits, (int64_t)N * P, vis, st);
+                           hipStream_t st) {
+  k_exp_quad_fwd<NB><<<(unsigned)pair_blocks(P), 64 * Quad<NB>::WAVES, 0, st>>>(Fpart, nchunks, P, eps, vis, saved);
+  return hipGetLastError();
 }
 
 template <int NB>
 hipError_t exp_quad_bwd_nb(const float* gV, const float* vis, const float* saved, int64_t P, float eps, float* W,
-                           float* table, float* part, hipStream_t st) {
-  constexpr int QP = QuadRule<NB>::QP, N = NB * NB;
-  float* Ytab = table;
-  float* wtab = table + (int64_t)QP * 64;
-  k_quad_table<NB><<<(QP + SHV_BLOCK - 1) / SHV_BLOCK, SHV_BLOCK, 0, st>>>(Ytab, wtab);
-  k_exp_quad_bwd<NB><<<dim3((unsigned)pair_blocks(P), kQuadSplits), SHV_BLOCK, 0, st>>>(gV, vis, saved, P, eps, part,
-                                                                                        Ytab, wtab);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_sum_chunks(part, kQuadSplits, (int64_t)N * P, W, st);
+                           hipStream_t st) {
+  k_exp_quad_bwd<NB><<<(unsigned)pair_blocks(P), 64 * Quad<NB>::WAVES, 0, st>>>(gV, vis, saved, P, eps, W);
+  return hipGetLastError();
 }
 
 }  // namespace shv

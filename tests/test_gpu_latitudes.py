@@ -53,3 +53,11 @@ def test_no_squarings_keep_the_linear_approximation():
     assert rel_l2(h["V"], o["V"].numpy()) <= 1e-5
     for key in GRADS:
         assert rel_l2(h[key], o[key].numpy()) <= 1e-4, key
+
+
+@pytest.mark.parametrize("n,P", [(1, 1), (2, 65), (3, 64), (5, 63), (6, 129), (7, 65), (8, 1), (8, 129)])
+def test_separable_quadrature_at_tile_edges(n, P):
+    """Every number of waves per block and of latitudes per wave."""
+    L = lib()
+    sc = scenegen.scene_random_shell(900 + n, P, 13, n)
+    _check(run_hip(sc, sc["grad_radiance"], flags=L.SHV_FLAG_EXP_QUADRATURE), sc, "quadrature")
