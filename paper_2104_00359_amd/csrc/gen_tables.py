@@ -323,6 +323,126 @@ def emit_lat(L):
             L.append(f"static constexpr unsigned char {name}_{n}[{n * n}] = {{" + ",".join(map(str, gid)) + "};")
 
 
+def real_basis(d, n):
+    """y_i, i < n^2, at unit directions d [..., 3], in 64 bits."""
+    x, y, z = d[..., 0], d[..., 1], d[..., 2]
+    cm, sm = [np.ones_like(x)], [np.zeros_like(x)]
+    for m in range(1, n):
+        cm.append(cm[-1] * x - sm[-1] * y)
+        sm.append(sm[-1] * x + cm[m - 1] * y)
+    out = [None] * (n * n)
+    for m in range(n):
+        norm = math.sqrt((2 * m + 1) / (4 * PI) * math.prod((2 * i - 1) / (2 * i) for i in range(1, m + 1)))
+        prev, cur = 0.0, np.full_like(z, norm * (math.sqrt(2) if m else 1.0))
+        for l in range(m, n):
+            if l > m:
+                a = math.sqrt((4 * l * l - 1) / (l * l - m * m))
+                b = math.sqrt(((l - 1) ** 2 - m * m) / (4 * (l - 1) ** 2 - 1)) if l > m + 1 else 0.0
+                prev, cur = cur, a * (z * cur - b * prev)
+            out[l * l + l + m] = cur * cm[m]
+            if m:
+                out[l * l + l - m] = cur * sm[m]
+    return np.stack(out, -1)
+
+
+def quarter_turn():
+    """K: the rotation by 90 degrees about x (y to z) on real SH vectors,
+    (K f)(w) = f(K^-1 w), by exact quadrature.  With Z(a) the rotation about z,
+    the rotation about y is K^-1 Z(a) K."""
+    n = MAX_BANDS
+    zs, ws = np.polynomial.legendre.leggauss(2 * n)
+    ph = np.arange(4 * n) * 2 * PI / (4 * n)
+    st = np.sqrt(1 - zs * zs)
+    d = np.stack([st[:, None] * np.cos(ph), st[:, None] * np.sin(ph), zs[:, None] + 0 * ph], -1).reshape(-1, 3)
+    w = np.repeat(ws * 2 * PI / (4 * n), 4 * n)
+    K = (real_basis(d, n) * w[:, None]).T @ real_basis(np.stack([d[:, 0], d[:, 2], -d[:, 1]], -1), n)
+    K[np.abs(K) < 1e-12] = 0.0
+    return K
+
+
+def z_turn(a, derivative=False):
+    """The rotation by a about z on real SH vectors, or its derivative at 0."""
+    N = MAX_BANDS ** 2
+    Z = np.zeros((N, N))
+    for i in range(N):
+        l, m = lm(i)
+        j = l * l + l - m
+        if derivative:
+            Z[i, j] -= m
+        else:
+            Z[i, i] = math.cos(m * a)
+            if m:
+                Z[i, j] = -math.sin(m * a)
+    return Z
+
+
+def turn_groups(n, ng=N_GROUPS):
+    """Bands l and orders m dealt to the waves of the product chain: the bands
+    for the rotations (block-diagonal in l), the orders for the products with a
+    zonal function (block-diagonal in m), each to the least loaded wave."""
+    out = []
+    for cost in ({l: 2 * l + 1 for l in range(n)}, {m: (n - m) * (2 if m else 1) for m in range(n)}):
+        load, grp = [0] * ng, {}
+        for k in sorted(cost, key=lambda k: -cost[k]):
+            g = load.index(min(load))
+            grp[k] = g
+            load[g] += cost[k]
+        out.append([grp[k] for k in range(n)])
+    return out
+
+
+def emit_turns(L):
+    """Rotations and rotation cotangents band by band, on coefficients scaled
+    as in shv_lat.h (entry m + l of band l), and the product chain's tables."""
+    K = quarter_turn()
+    Lz = z_turn(0.0, True)
+    Ly = K.T @ Lz @ K
+    A = K.T @ z_turn(-PI / 2) @ K   # takes x to z
+    Lx = A.T @ Lz @ A
+    s = np.array([1.0 if lm(i)[1] == 0 else math.sqrt(0.5) for i in range(MAX_BANDS ** 2)])
+    L.append("// Rotations of SH vectors band by band (shv_prod_impl.h).")
+    for l in range(MAX_BANDS):
+        b = slice(l * l, (l + 1) ** 2)
+        for name, M in (("turn", K[b, b]), ("unturn", K[b, b].T)):
+            L.append(f"__device__ __forceinline__ void shv_{name}_l{l}(const float* v, float* o) {{")
+            for i in range(2 * l + 1):
+                e = None
+                for j in range(2 * l + 1):
+                    c = M[i, j] * s[b][i] / s[b][j]
+                    if abs(c) < 1e-12:
+                        continue
+                    t = f"v[{j}]" if abs(c - 1) < 1e-12 else f"{flit(c)} * v[{j}]"
+                    e = t if e is None else f"fmaf({flit(c)}, v[{j}], {e})"
+                L.append(f"  o[{i}] = {e};")
+            L.append("}")
+        # gx = -<Ly v, t>, gy = <Lx v, t>, with 1 / scale^2 (up to 4 pi): the
+        # generators are antisymmetric, so each pair of entries is one term
+        L.append(f"__device__ __forceinline__ void shv_torque_l{l}(const float* v, const float* t, float& gx, float& gy) {{")
+        for var, M in (("gx", -Ly[b, b]), ("gy", Lx[b, b])):
+            for i in range(2 * l + 1):
+                for j in range(i):
+                    c = M[i, j] / (s[b][i] * s[b][j])
+                    if abs(c) > 1e-12:
+                        L.append(f"  {var} = fmaf({flit(c)}, fmaf(v[{j}], t[{i}], -(v[{i}] * t[{j}])), {var});")
+        L.append("}")
+    L.append("// A zonal function at the latitudes of shv_lat_rows: twice (2 l + 1) / (4 pi) P_l(z) w^(1/3)")
+    L.append("// (the sum and difference of the values at z and -z), once at the equator; and the waves'")
+    L.append("// bands and orders.")
+    for n in range(LAT_MIN_BANDS, MAX_BANDS + 1):
+        zs, ws = np.polynomial.legendre.leggauss((3 * n - 3) // 2 + 1)
+        vals = []
+        for z, w in [(z, w) for z, w in zip(zs, ws) if z > 1e-9] + [(z, w) for z, w in zip(zs, ws) if abs(z) <= 1e-9]:
+            z = z if z > 1e-9 else 0.0
+            for l in range(n):
+                c = np.zeros(l + 1)
+                c[l] = 1.0
+                vals.append((2.0 if z else 1.0) * (2 * l + 1) / (4 * PI) * np.polynomial.legendre.legval(z, c) * w ** (1 / 3))
+        L.append(f"static constexpr float shv_zonal_rows_{n}[{len(vals)}] = {{" + ",".join(flit(v) for v in vals) + "};")
+        lg, mg = turn_groups(n)
+        L.append(f"static constexpr unsigned char SHV_TURN_L_{n}[{n}] = {{" + ",".join(map(str, lg)) + "};")
+        L.append(f"static constexpr unsigned char SHV_TURN_M_{n}[{n}] = {{" + ",".join(map(str, mg)) + "};")
+
+
 def emit_quad(L):
     """The product rule of degree 8 n - 1: 4 n Gauss-Legendre latitudes, as
     the rows and weights of the pairs +-z, and 8 n azimuths (j + 1/2) 2 pi / 8 n,
@@ -577,6 +697,7 @@ def emit_gaunt(path):
     emit_quad(L)
     L.append("")
     emit_lat(L)
+    emit_turns(L)
     L.append("")
     for n in range(1, MAX_BANDS + 1):
         supp = transfer_support(n)

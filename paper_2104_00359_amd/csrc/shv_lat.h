@@ -213,9 +213,7 @@ __device__ __forceinline__ void lat_row(const float (&e)[NB * NB], const float (
 }
 
 // The outputs of group G (-1: all): o = e * e (SQUARE) or o = 2 (h * e).
-// ROLLED keeps the loop over the pairs, for kernels whose unrolled code would
-// leave the instruction cache.
-template <int NB, int G, bool SQUARE, bool ROLLED = false>
+template <int NB, int G, bool SQUARE>
 __device__ __forceinline__ void lat_product(const float (&e)[NB * NB], const float (&h)[NB * NB],
                                             float (&o)[NB * NB]) {
   constexpr int N = NB * NB, QP = Lat<NB>::QP;
@@ -223,13 +221,8 @@ __device__ __forceinline__ void lat_product(const float (&e)[NB * NB], const flo
   for (int i = 0; i < N; ++i)
     if (G < 0 || group_of<NB>(i) == G) o[i] = 0.0f;
   const float* __restrict__ Q = LatTab<NB>::rows();
-  if constexpr (ROLLED) {
-#pragma unroll 1
-    for (int t = 0; t < LatTab<NB>::PAIRS; ++t) lat_row<NB, G, SQUARE, false>(e, h, Q + t * QP, o);
-  } else {
 #pragma unroll
-    for (int t = 0; t < LatTab<NB>::PAIRS; ++t) lat_row<NB, G, SQUARE, false>(e, h, Q + t * QP, o);
-  }
+  for (int t = 0; t < LatTab<NB>::PAIRS; ++t) lat_row<NB, G, SQUARE, false>(e, h, Q + t * QP, o);
   if constexpr (LatTab<NB>::EQ > 0) lat_row<NB, G, SQUARE, true>(e, h, Q + LatTab<NB>::PAIRS * QP, o);
   const float t0 = 2.0f * e[0];
 #pragma unroll

@@ -62,3 +62,34 @@ def test_output_groups_are_whole_orders(gen, n):
         assert sorted(i for g in groups for i in g) == list(range(n * n))
         owner = {abs(gen.lm(i)[1]): g for g, members in enumerate(groups) for i in members}
         assert all(owner[abs(gen.lm(i)[1])] == g for g, members in enumerate(groups) for i in members)
+
+
+def test_sphere_frame_rotation_and_its_generators(gen):
+    """R = K^-1 Z(-theta) K Z(-phi) takes the direction (theta, phi) to +z, and the generators used by the
+    adjoint are the derivatives of the rotations about x and y; 1e-12 is a few thousand roundings of 64 bits."""
+    n = gen.MAX_BANDS
+    K = gen.quarter_turn()
+    assert np.allclose(K @ K.T, np.eye(n * n), atol=1e-12)
+    assert all(K[i, j] == 0 for i in range(n * n) for j in range(n * n) if gen.lm(i)[0] != gen.lm(j)[0])
+    for th, ph in ((0.7, 1.9), (0.0, 0.0), (math.pi, -2.0), (1.3, 0.4)):
+        d = np.array([math.sin(th) * math.cos(ph), math.sin(th) * math.sin(ph), math.cos(th)])
+        f = K.T @ gen.z_turn(-th) @ K @ gen.z_turn(-ph) @ gen.real_basis(d, n)
+        want = [math.sqrt((2 * gen.lm(i)[0] + 1) / (4 * math.pi)) if gen.lm(i)[1] == 0 else 0.0 for i in range(n * n)]
+        assert np.allclose(f, want, atol=1e-12)
+    Lz = gen.z_turn(0.0, True)
+    A = K.T @ gen.z_turn(-math.pi / 2) @ K
+    rng = np.random.default_rng(1)
+    f, d = rng.standard_normal(n * n), rng.standard_normal((7, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    # (L f)(w) = -(axis x w) . grad f; the coordinates' own functions (band 1) give it exactly
+    for L, axis in ((A.T @ Lz @ A, (1.0, 0, 0)), (K.T @ Lz @ K, (0, 1.0, 0)), (Lz, (0, 0, 1.0))):
+        for c in range(3):
+            e = np.zeros(n * n)
+            e[(3, 1, 2)[c]] = math.sqrt(4 * math.pi / 3)   # the function w -> w_c
+            assert np.allclose(gen.real_basis(d, n) @ (L @ e), -np.cross(axis, d)[:, c], atol=1e-12)
+
+
+@pytest.mark.parametrize("n", [6, 7, 8])
+def test_waves_of_the_product_chain_own_every_band_and_order(gen, n):
+    bands, orders = gen.turn_groups(n)
+    assert len(bands) == len(orders) == n and set(bands) == set(orders) == {0, 1, 2, 3}
