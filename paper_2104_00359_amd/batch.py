@@ -133,6 +133,8 @@ def scene_buffers(scene: dict, device, eps=3.0, n_squarings=4, flags=0, grads=GR
 
     S = np.asarray(scene["spheres"]).reshape(-1, 4).shape[0]
     gB = scene.get("grad_radiance")
+    if gB is not None and np.size(gB) == 0:
+        gB = np.zeros(1, np.float32)  # an empty tensor has no address, which would read as "no cotangent"
     return SceneBuffers(points=t(np.asarray(scene["points"]).reshape(-1, 3).T),
                         normals=t(np.asarray(scene["normals"]).reshape(-1, 3).T),
                         albedo=t(scene["albedo"]), spheres=t(np.asarray(scene["spheres"]).reshape(S, 4)),

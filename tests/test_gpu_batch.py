@@ -206,3 +206,19 @@ def test_receiver_ranges_reproduce_whole_scene_bitwise():
     torch.cuda.synchronize()
     for b, ref in zip(bufs, refs):
         _assert_same(collect(b), ref, f"ranges P={b.P}")
+
+
+def test_empty_scene_has_zero_gradients_in_used_memory():
+    """A scene without receivers still has a cotangent: its sphere and lighting
+    gradients are written (zeros), whatever their memory held before."""
+    from paper_2104_00359_amd import batch, ops
+    dev = torch.device("cuda", 0)
+    ops.ensure_init(dev)
+    b = batch.scene_buffers(scenegen.scene_random_shell(90, 0, 5, 5), dev)
+    rb = batch.RenderBatch([b], dev)
+    b.out["arena"].fill_(255)
+    rb.forward()
+    rb.backward()
+    torch.cuda.synchronize()
+    got = collect(b)
+    assert not got["grad_spheres"].any() and not got["grad_light"].any()
