@@ -202,13 +202,15 @@ hipError_t launch_batch_finalize(const void* table, int64_t blocks, hipStream_t 
 bool exp_four_waves(int nb, int64_t P, uint32_t flags, bool batched) {
   if (flags & SHV_FLAG_EXP_ONE_WAVE) return false;
   if (flags & SHV_FLAG_EXP_FOUR_WAVES) return true;
-  // Up to 6 bands a receiver's whole squaring fits one lane's registers, and
-  // one receiver per lane (no LDS exchange, no barriers) is faster than four
-  // waves per 64 receivers; a launch then has 4x fewer blocks, so a single
-  // scene takes it only from 256 blocks (65,536 receivers) up.  At 7 and 8
-  // bands the four-wave layout is faster for the adjoint (both layouts give
-  // identical bits).
-  return !(nb <= 6 && (batched || P >= 65536));
+  // One receiver per lane needs no exchange through LDS and no barriers, but a
+  // launch then has 4x fewer blocks and a wave has 4x the work, so a single
+  // scene takes it only once it fills the chip.  Up to 6 bands that is from 256
+  // blocks (65,536 receivers) up.  At 7 and 8 bands forward + adjoint take
+  // 128 us against 109 in four waves at 65,536 receivers (8 bands, k = 4), 143
+  // against 154 at 98,304 and 344 against 440 at 262,144.  A batch's up to 6
+  // bands always take it; above, a batch counts as four waves per 64 receivers
+  // and its kernels apply the size rule to the whole launch (batch_wide).
+  return !(nb <= 6 ? batched || P >= 65536 : !batched && P >= SHV_EXP_WIDE_RECEIVERS);
 }
 
 // ---------------------------------------------------------------------------

@@ -28,6 +28,8 @@
 
 #pragma once
 
+#include <type_traits>
+
 #include "shv_batch.h"
 #include "shv_lat.h"
 #include "shv_launch.h"
@@ -274,10 +276,19 @@ __device__ __forceinline__ void exp_fwd1_item(const float* __restrict__ Fpart, i
   }
 }
 
+// Waves per SIMD asked of the one-wave forward: what its registers allow
+// (about 56 at 5 bands, 110 at 6, 141 at 7, 170 at 8).  Unasked, the compiler
+// adds accumulation registers for the shading's matrix steps and 6 bands and
+// above run one wave per SIMD fewer.
+template <int NB>
+struct Fwd1Waves {
+  static constexpr int VALUE = NB >= 7 ? 3 : NB == 6 ? 4 : 8;
+};
+
 template <int NB, bool SHADE>
-__global__ __launch_bounds__(SHV_BLOCK) void k_exp_fwd(const float* __restrict__ Fpart, int nchunks, int64_t P,
-                                                       float eps, int k, float* __restrict__ vis,
-                                                       float* __restrict__ saved, ShadeArgs sa) {
+__global__ __launch_bounds__(SHV_BLOCK, Fwd1Waves<NB>::VALUE) void k_exp_fwd(
+    const float* __restrict__ Fpart, int nchunks, int64_t P, float eps, int k, float* __restrict__ vis,
+    float* __restrict__ saved, ShadeArgs sa) {
   if constexpr (SHADE) {
     __shared__ float Ms[MSupp<NB>::SIZE];
     exp_fwd1_item<NB, SHADE>(Fpart, nchunks, P, eps, k, vis, saved, sa, blockIdx.x, Ms);
@@ -286,11 +297,39 @@ __global__ __launch_bounds__(SHV_BLOCK) void k_exp_fwd(const float* __restrict__
   }
 }
 
+// At 7 and 8 bands the one-wave adjoint keeps E_j in LDS, one column per lane:
+// with it the cotangent, the outputs and one row's Fourier coefficients are all
+// the registers hold, 256 and two waves per SIMD instead of 390 and one (222 us
+// for 262,144 receivers at 8 bands, k = 4; four waves per receiver take 315).
+// What bounds it is the FP32 issue of the rows: a wave issues one instruction
+// in about 5 cycles, and two waves share a SIMD.
+template <int NB>
+struct Bwd1Lds {
+  static constexpr bool USE = NB >= 7;
+};
+
+// LDS of the one-wave adjoint; E overlays the shading's (a barrier separates them).
+template <int NB>
+union Exp1BwdShared {
+  struct {
+    LightTile LT;
+    float Ms[MSupp<NB>::SIZE];
+  } s;
+  float E[Bwd1Lds<NB>::USE ? SHV_WAVES_PER_BLOCK : 1][Bwd1Lds<NB>::USE ? NB * NB : 1][64];
+};
+
+// n, opaque to the compiler: row offsets formed from it are not kept in
+// registers over the code between two uses.
+__device__ __forceinline__ int64_t fresh(int64_t n) {
+  asm volatile("" : "+s"(n));
+  return n;
+}
+
 template <int NB, bool SHADE>
 __device__ __forceinline__ void exp_bwd1_item(const float* __restrict__ gIn, const float* __restrict__ vis,
                                               const float* __restrict__ saved, int64_t P, float eps, int k,
                                               float* __restrict__ Wout, const ShadeArgs& sa, int64_t bx,
-                                              LightTile* LTp, float* Ms) {
+                                              LightTile* LTp, float* Ms, float (*El)[64]) {
   constexpr int N = NB * NB;
   const int64_t p = bx * SHV_BLOCK + threadIdx.x;
   const bool ok = p < P;
@@ -336,6 +375,7 @@ __device__ __forceinline__ void exp_bwd1_item(const float* __restrict__ gIn, con
       }
     }
     vbar_rows<NB, N>([](int r) { return r; }, H, Ms, w, Eb);
+    if constexpr (Bwd1Lds<NB>::USE) __syncthreads();  // E overlays the tile and M
     if (!ok) return;  // no barriers or matrix steps below
   } else {
 #pragma unroll
@@ -344,32 +384,54 @@ __device__ __forceinline__ void exp_bwd1_item(const float* __restrict__ gIn, con
   const float c = saved[p];
   const float ec = expf(c);
   const float cbar = cbar_canonical<NB>(Eb, E);  // d/dc of exp(c) E_k . Vbar = V . Vbar
+  if (k == 0) {  // E_0 = V / exp(c) when there is no squaring
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if (k == 0) E[i] = (E[i] / ec) * coef_scale<NB>(i);  // E_0 itself when there is no squaring
-    Eb[i] = (ec * Eb[i]) * cot_scale<NB>(i);
+    for (int i = 0; i < N; ++i) {
+      E[i] = (E[i] / ec) * coef_scale<NB>(i);
+      Eb[i] = (ec * Eb[i]) * cot_scale<NB>(i);
+    }
+    exp_epilogue<NB>(E, Eb, cbar, eps, k, P, p, Wout, [](int) { return true; });
+    return;
   }
-  for (int j = k - 1; j >= 0; --j) {
-    const float* src = saved + (int64_t)(1 + j * N) * P + p;
 #pragma unroll
-    for (int i = 0; i < N; ++i) E[i] = src[(int64_t)i * P];
-    SqGroup<NB, -1>::adj(Eb, E, T);  // Ebar_j = 2 (Ebar_{j+1} * E_j)
+  for (int i = 0; i < N; ++i) Eb[i] = (ec * Eb[i]) * cot_scale<NB>(i);
+  const int col = threadIdx.x & 63;
+  for (int j = k - 1; j >= 0; --j) {
+    const int64_t Pj = Bwd1Lds<NB>::USE ? fresh(P) : P;
+    const float* src = saved + (int64_t)(1 + j * N) * Pj + p;
+#pragma unroll
+    for (int i = 0; i < N; ++i) E[i] = src[(int64_t)i * Pj];
+    if constexpr (Bwd1Lds<NB>::USE) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) El[i][col] = E[i];
+      // E is read again per row, and the rows stay apart
+      lat_product<NB, -1, false>([&](int i) { return El[i][col]; }, Eb, T, [] {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    } else {
+      SqGroup<NB, -1>::adj(Eb, E, T);  // Ebar_j = 2 (Ebar_{j+1} * E_j)
+    }
 #pragma unroll
     for (int i = 0; i < N; ++i) Eb[i] = T[i];
   }
-  exp_epilogue<NB>(E, Eb, cbar, eps, k, P, p, Wout, [](int) { return true; });
+  if constexpr (Bwd1Lds<NB>::USE) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) E[i] = El[i][col];
+  }
+  exp_epilogue<NB>(E, Eb, cbar, eps, k, Bwd1Lds<NB>::USE ? fresh(P) : P, p, Wout, [](int) { return true; });
 }
 
 template <int NB, bool SHADE>
-__global__ __launch_bounds__(SHV_BLOCK, NB <= 6 ? 2 : 1) void k_exp_bwd(const float* __restrict__ gIn, const float* __restrict__ vis,
+__global__ __launch_bounds__(SHV_BLOCK, 2) void k_exp_bwd(const float* __restrict__ gIn, const float* __restrict__ vis,
                                                        const float* __restrict__ saved, int64_t P, float eps, int k,
                                                        float* __restrict__ Wout, ShadeArgs sa) {
-  if constexpr (SHADE) {
-    __shared__ LightTile LT;
-    __shared__ float Ms[MSupp<NB>::SIZE];
-    exp_bwd1_item<NB, SHADE>(gIn, vis, saved, P, eps, k, Wout, sa, blockIdx.x, &LT, Ms);
+  if constexpr (SHADE || Bwd1Lds<NB>::USE) {
+    __shared__ Exp1BwdShared<NB> sh;
+    exp_bwd1_item<NB, SHADE>(gIn, vis, saved, P, eps, k, Wout, sa, blockIdx.x, &sh.s.LT, sh.s.Ms,
+                             sh.E[Bwd1Lds<NB>::USE ? threadIdx.x >> 6 : 0]);
   } else {
-    exp_bwd1_item<NB, SHADE>(gIn, vis, saved, P, eps, k, Wout, sa, blockIdx.x, nullptr, nullptr);
+    exp_bwd1_item<NB, SHADE>(gIn, vis, saved, P, eps, k, Wout, sa, blockIdx.x, nullptr, nullptr, nullptr);
   }
 }
 
@@ -465,9 +527,9 @@ __device__ __forceinline__ void exp_fwd4_item(const float* __restrict__ Fpart, i
 }
 
 template <int NB, bool SHADE>
-__global__ __launch_bounds__(SHV_BLOCK) void k_exp_fwd4(const float* __restrict__ Fpart, int nchunks, int64_t P,
-                                                        float eps, int k, float* __restrict__ vis,
-                                                        float* __restrict__ saved, ShadeArgs sa) {
+__global__ __launch_bounds__(SHV_BLOCK, NB == 8 ? 4 : 1) void k_exp_fwd4(
+    const float* __restrict__ Fpart, int nchunks, int64_t P, float eps, int k, float* __restrict__ vis,
+    float* __restrict__ saved, ShadeArgs sa) {
   __shared__ Exp4FwdShared<NB> sh;
   exp_fwd4_item<NB, SHADE>(Fpart, nchunks, P, eps, k, vis, saved, sa, blockIdx.x, sh);
 }
@@ -706,8 +768,22 @@ hipError_t exp_bwd_nb(const float* gIn, const float* vis, const float* saved, in
 // Batched phases of the fused render path: scenes with NB bands whose
 // exponential uses the four-wave layout (FOUR) or the one-wave layout; one
 // block per item of the group's item space (blocks beyond it exit).
+//
+// The four-wave group's grid has one block per 64 receivers.  At 7 and 8 bands,
+// once the whole group reaches SHV_EXP_WIDE_RECEIVERS, the first quarter of a
+// scene's blocks take 256 receivers each, one per lane, and the others exit:
+// the size rule of single scenes, taken over the launch, with the same grid and
+// the same bits.  (Every fourth block would be the same work on two of the
+// eight XCDs, which consecutive blocks go round.)  A range starts at a multiple
+// of 256 receivers, so the quarter covers it exactly.
+template <int NB>
+__device__ __forceinline__ bool batch_wide(const BatchView& v, const BatchScene& S) {
+  return NB >= 7 && v.h->total_exp[1][NB] * 64 >= SHV_EXP_WIDE_RECEIVERS && !(S.flags & SHV_FLAG_EXP_FOUR_WAVES);
+}
+
 template <int NB, bool FOUR>
-__global__ __launch_bounds__(SHV_BLOCK) void k_batch_exp_fwd(const char* __restrict__ table) {
+__global__ __launch_bounds__(SHV_BLOCK, FOUR && NB < 7 ? 1 : Fwd1Waves<NB>::VALUE) void k_batch_exp_fwd(
+    const char* __restrict__ table) {
   __shared__ Exp4FwdShared<NB> sh;
   const BatchView v(table);
   const int64_t item = blockIdx.x;
@@ -715,22 +791,48 @@ __global__ __launch_bounds__(SHV_BLOCK) void k_batch_exp_fwd(const char* __restr
   const BatchScene S = in_global(v.scene_of_exp(FOUR, NB, item));
   const int64_t bx = S.exp_block0 + (item - S.off_exp);
   const ShadeArgs sa{S.normals, S.albedo, S.M, S.radiance, nullptr, nullptr, nullptr};
-  if constexpr (FOUR) exp_fwd4_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa, bx, sh);
-  else exp_fwd1_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa, bx, &sh.X[0][0][0]);
+  if constexpr (FOUR) {
+    if constexpr (NB >= 7) {
+      if (batch_wide<NB>(v, S)) {  // uniform
+        if (4 * (item - S.off_exp) >= S.n_exp) return;
+        exp_fwd1_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa,
+                                S.exp_block0 / 4 + (item - S.off_exp), &sh.X[0][0][0]);
+        return;
+      }
+    }
+    exp_fwd4_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa, bx, sh);
+  } else {
+    exp_fwd1_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa, bx, &sh.X[0][0][0]);
+  }
 }
 
 template <int NB, bool FOUR>
-__global__ __launch_bounds__(SHV_BLOCK, FOUR || NB <= 6 ? 2 : 1) void k_batch_exp_bwd(const char* __restrict__ table) {
-  __shared__ Exp4BwdShared<NB> sh;
+union BatchBwdShared {
+  std::conditional_t<FOUR, Exp4BwdShared<NB>, Exp1BwdShared<NB>> own;
+  Exp1BwdShared<NB> one;
+};
+
+template <int NB, bool FOUR>
+__global__ __launch_bounds__(SHV_BLOCK, 2) void k_batch_exp_bwd(const char* __restrict__ table) {
+  __shared__ BatchBwdShared<NB, FOUR> sh;
   const BatchView v(table);
   const int64_t item = blockIdx.x;
   if (item >= v.h->total_exp[FOUR][NB]) return;
   const BatchScene S = in_global(v.scene_of_exp(FOUR, NB, item));
   if (!S.grad_radiance) return;  // uniform: scene packed without a cotangent
-  const int64_t bx = S.exp_block0 + (item - S.off_exp);
+  int64_t bx = S.exp_block0 + (item - S.off_exp);
   const ShadeArgs sa{S.normals, S.albedo, S.M, nullptr, S.grad_normals, S.grad_albedo, S.grad_light ? S.lp : nullptr};
-  if constexpr (FOUR) exp_bwd4_item<NB, true>(S.grad_radiance, S.vis, S.saved, S.P, S.eps, S.k, S.W, sa, bx, sh);
-  else exp_bwd1_item<NB, true>(S.grad_radiance, S.vis, S.saved, S.P, S.eps, S.k, S.W, sa, bx, &sh.s.LT, sh.s.Ms);
+  if constexpr (FOUR) {
+    if (NB < 7 || !batch_wide<NB>(v, S)) {  // uniform
+      exp_bwd4_item<NB, true>(S.grad_radiance, S.vis, S.saved, S.P, S.eps, S.k, S.W, sa, bx, sh.own);
+      return;
+    }
+    if (4 * (item - S.off_exp) >= S.n_exp) return;
+    bx = S.exp_block0 / 4 + (item - S.off_exp);
+  }
+  if constexpr (!FOUR || NB >= 7)
+    exp_bwd1_item<NB, true>(S.grad_radiance, S.vis, S.saved, S.P, S.eps, S.k, S.W, sa, bx, &sh.one.s.LT, sh.one.s.Ms,
+                            sh.one.E[Bwd1Lds<NB>::USE ? threadIdx.x >> 6 : 0]);
 }
 
 template <int NB>

@@ -99,11 +99,11 @@ __device__ __forceinline__ constexpr bool lat_has(int m) { return G < 0 || group
 template <int NB>
 __device__ __forceinline__ constexpr int lat_at(int m) { return m * NB - m * (m - 1) / 2; }
 
-// Fourier coefficients of the function e at z (index 0) and -z (1), or at the
-// equator (EQ; the odd terms vanish); without its mean unless MEAN.
-template <int NB, bool EQ, bool MEAN>
-__device__ __forceinline__ void lat_up(const float (&e)[NB * NB], const float* __restrict__ Q, float (&A)[2][NB],
-                                       float (&B)[2][NB]) {
+// Fourier coefficients of the function with coefficients e(i) at z (index 0) and
+// -z (1), or at the equator (EQ; the odd terms vanish); without its mean unless
+// MEAN.
+template <int NB, bool EQ, bool MEAN, class Coef>
+__device__ __forceinline__ void lat_up(Coef e, const float* __restrict__ Q, float (&A)[2][NB], float (&B)[2][NB]) {
 #pragma unroll
   for (int m = 0; m < NB; ++m) {
     float a[2] = {0.0f, 0.0f}, b[2] = {0.0f, 0.0f};
@@ -113,8 +113,8 @@ __device__ __forceinline__ void lat_up(const float (&e)[NB * NB], const float* _
       const int s = (l - m) & 1;
       if ((l == 0 && !MEAN) || (EQ && s)) continue;
       const float t = Q[lat_at<NB>(m) + l - m];
-      a[s] = on[s] ? fmaf(t, e[idx(l, m)], a[s]) : t * e[idx(l, m)];
-      if (m > 0) b[s] = on[s] ? fmaf(t, e[idx(l, -m)], b[s]) : t * e[idx(l, -m)];
+      a[s] = on[s] ? fmaf(t, e(idx(l, m)), a[s]) : t * e(idx(l, m));
+      if (m > 0) b[s] = on[s] ? fmaf(t, e(idx(l, -m)), b[s]) : t * e(idx(l, -m));
       on[s] = true;
     }
     A[0][m] = EQ ? a[0] : a[0] + a[1];
@@ -184,12 +184,12 @@ __device__ __forceinline__ void lat_mul(const float (&A)[NB], const float (&B)[N
 
 // One row of a product: o += its share, for the orders of group G.  SQUARE:
 // (e - mean)^2, else twice (e - mean) h.
-template <int NB, int G, bool SQUARE, bool EQ>
-__device__ __forceinline__ void lat_row(const float (&e)[NB * NB], const float (&h)[NB * NB],
-                                        const float* __restrict__ Q, float (&o)[NB * NB]) {
+template <int NB, int G, bool SQUARE, bool EQ, class Coef>
+__device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const float* __restrict__ Q,
+                                        float (&o)[NB * NB]) {
   float A[2][NB], B[2][NB], X[2][NB], Y[2][NB];
   lat_up<NB, EQ, false>(e, Q, A, B);
-  if constexpr (!SQUARE) lat_up<NB, EQ, true>(h, Q, X, Y);
+  if constexpr (!SQUARE) lat_up<NB, EQ, true>([&](int i) { return h[i]; }, Q, X, Y);
 #pragma unroll
   for (int m = 0; m < NB; ++m) {
     if (!lat_has<NB, G>(m)) continue;
@@ -212,25 +212,37 @@ __device__ __forceinline__ void lat_row(const float (&e)[NB * NB], const float (
   }
 }
 
-// The outputs of group G (-1: all): o = e * e (SQUARE) or o = 2 (h * e).
-template <int NB, int G, bool SQUARE>
-__device__ __forceinline__ void lat_product(const float (&e)[NB * NB], const float (&h)[NB * NB],
-                                            float (&o)[NB * NB]) {
+// The outputs of group G (-1: all): o = e * e (SQUARE) or o = 2 (h * e), e(i)
+// the coefficients of e.  between() is called before each row.
+template <int NB, int G, bool SQUARE, class Coef, class Between>
+__device__ __forceinline__ void lat_product(Coef e, const float (&h)[NB * NB], float (&o)[NB * NB], Between between) {
   constexpr int N = NB * NB, QP = Lat<NB>::QP;
 #pragma unroll
   for (int i = 0; i < N; ++i)
     if (G < 0 || group_of<NB>(i) == G) o[i] = 0.0f;
   const float* __restrict__ Q = LatTab<NB>::rows();
 #pragma unroll
-  for (int t = 0; t < LatTab<NB>::PAIRS; ++t) lat_row<NB, G, SQUARE, false>(e, h, Q + t * QP, o);
-  if constexpr (LatTab<NB>::EQ > 0) lat_row<NB, G, SQUARE, true>(e, h, Q + LatTab<NB>::PAIRS * QP, o);
-  const float t0 = 2.0f * e[0];
+  for (int t = 0; t < LatTab<NB>::PAIRS; ++t) {
+    between();
+    lat_row<NB, G, SQUARE, false>(e, h, Q + t * QP, o);
+  }
+  if constexpr (LatTab<NB>::EQ > 0) {
+    between();
+    lat_row<NB, G, SQUARE, true>(e, h, Q + LatTab<NB>::PAIRS * QP, o);
+  }
+  const float t0 = 2.0f * e(0);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     if (G >= 0 && group_of<NB>(i) != G) continue;
-    if constexpr (SQUARE) o[i] = i == 0 ? fmaf(e[0], e[0], o[0]) : fmaf(t0, e[i], o[i]);
+    if constexpr (SQUARE) o[i] = i == 0 ? fmaf(e(0), e(0), o[0]) : fmaf(t0, e(i), o[i]);
     else o[i] = fmaf(t0, h[i], o[i]);
   }
+}
+
+template <int NB, int G, bool SQUARE>
+__device__ __forceinline__ void lat_product(const float (&e)[NB * NB], const float (&h)[NB * NB],
+                                            float (&o)[NB * NB]) {
+  lat_product<NB, G, SQUARE>([&](int i) { return e[i]; }, h, o, [] {});
 }
 
 }  // namespace shv

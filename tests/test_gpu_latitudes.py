@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import scenegen
-from gpu_helpers import lib, rel_l2, run_hip, run_render
+from gpu_helpers import collect, lib, rel_l2, run_hip, run_render
 from oracle import method
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +61,33 @@ def test_separable_quadrature_at_tile_edges(n, P):
     L = lib()
     sc = scenegen.scene_random_shell(900 + n, P, 13, n)
     _check(run_hip(sc, sc["grad_radiance"], flags=L.SHV_FLAG_EXP_QUADRATURE), sc, "quadrature")
+
+
+@pytest.mark.parametrize("n", [7, 8])
+def test_large_launches_keep_the_four_wave_bits(n):
+    """From 98,304 receivers of a scene, or of a batch's four-wave group, a lane
+    takes a whole receiver; below, and for a scene that asks for four waves, it
+    does not.  Ragged ends, a range that starts inside its scene, and a small
+    scene beside large ones, against the four-wave layout bit for bit."""
+    import torch
+    from paper_2104_00359_amd import batch, ops
+    L = lib()
+    dev = torch.device("cuda", 0)
+    ops.ensure_init(dev)
+    scenes = [scenegen.scene_random_shell(1000 + n + i, P, 3, n) for i, P in enumerate((98305, 33001, 65, 700))]
+    flags = (0, 0, 0, L.SHV_FLAG_EXP_FOUR_WAVES)
+    refs = [run_render(sc, sc["grad_radiance"], flags=L.SHV_FLAG_EXP_FOUR_WAVES) for sc in scenes]
+    single = run_render(scenes[0], scenes[0]["grad_radiance"])
+    bufs = [batch.scene_buffers(sc, dev, flags=f) for sc, f in zip(scenes, flags)]
+    for b in bufs:
+        b.allocate(dev)
+    calls = [[bufs[0].record(0, 512, defer=True)],                                           # below the line
+             [bufs[0].record(512, 98305), bufs[2].record(), bufs[3].record(), bufs[1].record()]]
+    for recs in calls:
+        tab = batch.Table(recs, dev)
+        tab.forward(torch.cuda.current_stream())
+        tab.backward(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for got, ref in [(single, refs[0])] + [(collect(b), r) for b, r in zip(bufs, refs)]:
+        for key in ("V", "B") + GRADS:
+            assert np.array_equal(got[key], ref[key]), key
