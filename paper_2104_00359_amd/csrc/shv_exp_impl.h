@@ -527,9 +527,9 @@ __device__ __forceinline__ void exp_fwd4_item(const float* __restrict__ Fpart, i
 }
 
 template <int NB, bool SHADE>
-__global__ __launch_bounds__(SHV_BLOCK, NB == 8 ? 4 : 1) void k_exp_fwd4(
-    const float* __restrict__ Fpart, int nchunks, int64_t P, float eps, int k, float* __restrict__ vis,
-    float* __restrict__ saved, ShadeArgs sa) {
+__global__ __launch_bounds__(SHV_BLOCK) void k_exp_fwd4(const float* __restrict__ Fpart, int nchunks, int64_t P,
+                                                        float eps, int k, float* __restrict__ vis,
+                                                        float* __restrict__ saved, ShadeArgs sa) {
   __shared__ Exp4FwdShared<NB> sh;
   exp_fwd4_item<NB, SHADE>(Fpart, nchunks, P, eps, k, vis, saved, sa, blockIdx.x, sh);
 }
