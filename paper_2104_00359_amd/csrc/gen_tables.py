@@ -154,6 +154,35 @@ def recurrence_constants():
     return gamma, lam, rho
 
 
+def pair_constants():
+    """The pair kernels' basis (shv_device.h).  With Q_l^m = d^m P_l / dz^m:
+         p_l = P_l / its leading coefficient (m = 0),
+         rho_l^m = Q_l^m / kappa, m >= 1, kappa = (2m - 1)!! where l - m is even and (2m + 1)!! where it is odd,
+         so rho_m^m = 1, rho_{m+1}^m = z, and Q_l^m = Q_{l-2}^m + (2l - 1) Q_{l-1}^{m-1} has one constant, ROW;
+         a_0 = 1 - t, a_l = (1 - t^2) P_l'(t) / its leading coefficient: the zonal terms, d a_l / dt = -(l + 1) p_l.
+       Returns (pair, row, row_k, row_0, cap_b, leg_b): y_lm g_l = pair a_l rho_l^m T_m (at m = 0, p_l for rho),
+       ROW, d rho_l^m / dz over rho_l^{m+1} (l - m even; 1 where odd) and at m = 0 d p_l / dz over rho_l^1, and the
+       recurrences' a_{l+1} = t a_l - cap_b a_{l-1}, p_{l+1} = t p_l - leg_b p_{l-1}."""
+    lead = lambda l, m: Fraction(_f(2 * l), 2 ** l * _f(l) * _f(l - m))  # noqa: E731
+    kappa = lambda m, odd: Fraction(dfact(2 * m + 1 if odd else 2 * m - 1))  # noqa: E731
+    pair = [[0.0] * MAX_BANDS for _ in range(MAX_BANDS)]
+    row = [[0.0] * MAX_BANDS for _ in range(MAX_BANDS)]
+    for l in range(MAX_BANDS):
+        # g_l = -2 pi u, -2 pi (1 - t^2) P_l'(t) / (l (l + 1))
+        zonal = -2 * PI if l == 0 else -2 * PI * float(lead(l, 1) / (l * (l + 1)))
+        for m in range(l + 1):
+            odd = (l - m) % 2
+            pair[l][m] = zonal * norm_c(l, m) * float(kappa(m, odd) if m else lead(l, 0))
+            if l >= m + 2 and m >= 1:
+                below = kappa(m - 1, odd) if m > 1 else lead(l - 1, 0)
+                row[l][m] = float((2 * l - 1) * below / kappa(m, odd))
+    row_k = [float((2 * m + 1) * (2 * m + 3)) for m in range(MAX_BANDS)]
+    row_0 = [0.0] + [float(kappa(1, (l - 1) % 2) / lead(l, 0)) for l in range(1, MAX_BANDS)]
+    cap_b = [0.0] + [(l - 1) * (l + 1) / ((2 * l - 1) * (2 * l + 1)) for l in range(1, MAX_BANDS)]
+    leg_b = [l * l / ((2 * l - 1) * (2 * l + 1)) for l in range(MAX_BANDS)]
+    return pair, row, row_k, row_0, cap_b, leg_b
+
+
 def clamped_cosine(l):
     if l == 0:
         return PI
@@ -297,10 +326,10 @@ def lat_rows(n):
 
 
 def emit_lat(L):
-    lamb = recurrence_constants()[1]
+    lamb = pair_constants()[0]
     for name, f in (("SHV_LAT_LAM", lambda m: (1.0 if m == 0 else math.sqrt(0.5)) / math.sqrt(4 * PI)),
                     ("SHV_LAT_LAMI", lambda m: 1.0 if m == 0 else math.sqrt(2.0))):
-        L.append(f"// LAMBDA[l][m] times {'the scale of a coefficient' if name.endswith('M') else '1 / (sqrt(4 pi) scale)'}.")
+        L.append(f"// PAIR[l][m] times {'the scale of a coefficient' if name.endswith('M') else '1 / (sqrt(4 pi) scale)'}.")
         L.append(f"static constexpr float {name}[{MAX_BANDS}][{MAX_BANDS}] = {{")
         for l in range(MAX_BANDS):
             L.append("  {" + ", ".join(flit(lamb[l][m] * f(m)) for m in range(MAX_BANDS)) + "},")
@@ -448,7 +477,7 @@ def emit_quad(L):
     the rows and weights of the pairs +-z, and 8 n azimuths (j + 1/2) 2 pi / 8 n,
     as the cosines and sines of m phi_j in the first quarter."""
     L.append("// Quadrature of the projected exponential (shv_quad_impl.h).")
-    lamb = recurrence_constants()[1]
+    lamb = pair_constants()[0]
     for n in range(1, MAX_BANDS + 1):
         zs, ws = np.polynomial.legendre.leggauss(4 * n)
         up = [(z, w) for z, w in zip(zs, ws) if z > 0]
@@ -463,7 +492,7 @@ def emit_quad(L):
                 for j in range(2 * n)) + "};")
     for name, f in (("norm", lambda l, m: (1.0 if m == 0 else math.sqrt(2.0)) / math.sqrt(4 * PI)),
                     ("lam", lambda l, m: lamb[l][abs(m)])):
-        L.append(f"// {'y_lm over its row entry' if name == 'norm' else 'LAMBDA[l][|m|]'}, by coefficient index.")
+        L.append(f"// {'y_lm over its row entry' if name == 'norm' else 'PAIR[l][|m|]'}, by coefficient index.")
         L.append(f"static constexpr float shv_coef_{name}[{MAX_BANDS ** 2}] = {{"
                  + ",".join(flit(f(*lm(i))) for i in range(MAX_BANDS ** 2)) + "};")
 
@@ -494,6 +523,11 @@ def emit_constants(path):
     table2("SHV_GAMMA", gamma)
     table2("SHV_LAMBDA", lam)
     table2("SHV_RHO", rho)
+    pair, row, row_k, row_0, cap_b, leg_b = pair_constants()
+    table2("SHV_PAIR", pair)
+    table2("SHV_ROW", row)
+    for name, t in (("SHV_ROW_K", row_k), ("SHV_ROW_0", row_0), ("SHV_CAP_B", cap_b), ("SHV_LEG_B", leg_b)):
+        lines.append(f"static constexpr float {name}[{MAX_BANDS}] = {{" + ", ".join(flit(v) for v in t) + "};")
     lines.append(f"static constexpr float SHV_AHAT[{MAX_BANDS}] = {{"
                  + ", ".join(flit(clamped_cosine(l)) for l in range(MAX_BANDS)) + "};")
     # log-cap zonal: g_l(t) = -eps * 2 pi/(2l+1) * (P_{l-1}(t) - P_{l+1}(t))

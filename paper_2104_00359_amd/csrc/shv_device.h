@@ -67,6 +67,43 @@ __device__ __forceinline__ void cap_zonal(float u, const float (&R)[NB + 1], flo
   for (int l = 1; l < NB; ++l) g[l] = SHV_CAPK[l] * (R[l + 1] - R[l - 1]);
 }
 
+// The pair kernels' basis: y_lm g_l = PAIR[l][|m|] a_l(t) rho_l^|m|(z) T_m, with
+// rho_l^m (m >= 1) d^m P_l / dz^m over a constant of (m, parity of l - m) and,
+// at m = 0, the monic Legendre polynomial p_l.  Those constants leave
+//   rho_m^m = 1,  rho_{m+1}^m = z,  rho_l^m = rho_{l-2}^m + ROW[l][m] rho_{l-1}^{m-1}
+// (from P'_{l+1} - P'_{l-1} = (2l + 1) P_l), one instruction per term where the
+// recurrence along l takes two, and every other factor goes into PAIR, which
+// the exponential kernels apply once per receiver.
+
+// p_l(z), l < NB.
+template <int NB>
+__device__ __forceinline__ void legendre_monic(float z, float (&r)[NB]) {
+  r[0] = 1.0f;
+  if constexpr (NB > 1) r[1] = z;
+#pragma unroll
+  for (int l = 2; l < NB; ++l)
+    r[l] = l == 2 ? fmaf(z, z, -SHV_LEG_B[1]) : fmaf(z, r[l - 1], -SHV_LEG_B[l - 1] * r[l - 2]);
+}
+
+// rho_l^m, m <= l < NB, from rho_l^{m-1} (m = 1: from p_l).
+template <int NB>
+__device__ __forceinline__ void legendre_row(int m, float z, const float (&below)[NB], float (&r)[NB]) {
+#pragma unroll
+  for (int l = m; l < NB; ++l)
+    r[l] = l == m ? 1.0f : l == m + 1 ? z : fmaf(SHV_ROW[l][m], below[l - 1], r[l - 2]);
+}
+
+// a_l(t): a_0 = u = 1 - t and a_l = s2 times the monic P_l'(t), s2 = 1 - t^2.
+// Formed from s2, small caps keep their digits; d a_l / dt = -(l + 1) p_l(t).
+template <int NB>
+__device__ __forceinline__ void cap_terms(float t, float u, float s2, float (&a)[NB]) {
+  a[0] = u;
+  if constexpr (NB > 1) a[1] = s2;
+  if constexpr (NB > 2) a[2] = t * s2;
+#pragma unroll
+  for (int l = 3; l < NB; ++l) a[l] = fmaf(t, a[l - 1], -SHV_CAP_B[l - 1] * a[l - 2]);
+}
+
 // y_i(x, y, z) for all i < NB^2 (unit vector).
 template <int NB>
 __device__ __forceinline__ void sh_eval(float x, float y, float z, float (&Y)[NB * NB]) {

@@ -16,8 +16,8 @@
 // Saved for the adjoint, coefficient-major: row 0 = c, rows 1 + j*N + i = E_j[i].
 //
 // The forward kernels also sum the sphere-chunk partials of F' in a fixed
-// order and apply F_lm = eps * LAMBDA[l][|m|] * F'_lm.  The adjoint writes
-// W = eps * LAMBDA * dLoss/dF, the weights the pair adjoint consumes.
+// order and apply F_lm = eps * PAIR[l][|m|] * F'_lm.  The adjoint writes
+// W = eps * PAIR * dLoss/dF, the weights the pair adjoint consumes.
 //
 // Two layouts, bitwise identical in their results: one receiver per lane
 // (large receiver counts), or each receiver's squarings spread over the 4
@@ -115,12 +115,12 @@ struct GroupRows {
   }
 };
 
-// LAMBDA[l][|m|] of coefficient i (constant-folded after unrolling).
-__device__ __forceinline__ float coef_lambda(int i) {
+// PAIR[l][|m|] of coefficient i (constant-folded after unrolling).
+__device__ __forceinline__ float coef_pair(int i) {
   int l = 0;
   while ((l + 1) * (l + 1) <= i) ++l;
   const int m = i - l * l - l;
-  return SHV_LAMBDA[l][m < 0 ? -m : m];
+  return SHV_PAIR[l][m < 0 ? -m : m];
 }
 
 // d loss / d c = V . Vbar, summed as four partial sums over the output groups
@@ -135,10 +135,10 @@ __device__ __forceinline__ float cbar_canonical(const float* vb, const float* v)
   return ((part[0] + part[1]) + part[2]) + part[3];
 }
 
-// eps LAMBDA_i, times the coefficient's scale where products go through latitudes.
+// PAIR_i, times the coefficient's scale where products go through latitudes.
 template <int NB>
 __device__ __forceinline__ float coef_weight(int i) {
-  if constexpr (!Lat<NB>::USE) return coef_lambda(i);
+  if constexpr (!Lat<NB>::USE) return coef_pair(i);
   int l = 0;
   while ((l + 1) * (l + 1) <= i) ++l;
   const int m = i - l * l - l;
@@ -168,7 +168,7 @@ __device__ __forceinline__ float exp_prologue(float (&E)[NB * NB], float eps, in
 }
 
 // Adjoint of the linear approximation and of the scaling; E holds E_0 and Eb
-// its cotangent.  Writes W_i = eps LAMBDA_i Fbar_i for coefficients i with
+// its cotangent.  Writes W_i = eps PAIR_i Fbar_i for coefficients i with
 // keep(i).
 template <int NB, class Keep>
 __device__ __forceinline__ void exp_epilogue(float (&E)[NB * NB], const float (&Eb)[NB * NB], float cbar, float eps,
@@ -188,7 +188,7 @@ __device__ __forceinline__ void exp_epilogue(float (&E)[NB * NB], const float (&
   }
   const float scale = __builtin_ldexpf(1.0f, -k);
   const float kdot = LAT ? fmaf(2.0f, dotm, dot) : dot * SHV_INV_4PI;
-  if (keep(0)) Wout[p] = eps * SHV_LAMBDA[0][0] * cbar * SHV_INV_SQRT_4PI;
+  if (keep(0)) Wout[p] = eps * SHV_PAIR[0][0] * cbar * SHV_INV_SQRT_4PI;
 #pragma unroll
   for (int l = 1; l < NB; ++l) {
 #pragma unroll
@@ -196,7 +196,7 @@ __device__ __forceinline__ void exp_epilogue(float (&E)[NB * NB], const float (&
       const int i = idx(l, m);
       if (!keep(i)) continue;
       const float gb = a * fmaf(E[i], kdot, Eb[i]);
-      const float lam = LAT ? SHV_LAT_LAMI[l][m < 0 ? -m : m] : SHV_LAMBDA[l][m < 0 ? -m : m];
+      const float lam = LAT ? SHV_LAT_LAMI[l][m < 0 ? -m : m] : SHV_PAIR[l][m < 0 ? -m : m];
       Wout[(int64_t)i * P + p] = eps * lam * scale * gb;
     }
   }

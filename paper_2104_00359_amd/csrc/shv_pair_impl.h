@@ -4,15 +4,16 @@
 // half-angle alpha = asin(r/|c - x|), t = cos(alpha); the log-blocker
 // -eps * 1[w . s >= t] (Eq. 13) has zonal coefficients g_l(t) about s, and
 // rotating them to s multiplies by y_lm(s).  The kernel accumulates
-//   F'_lm(x) = sum_i g_l(t_i) r_l^|m|(s_z) T_m(s_x, s_y)
-// in registers; the constant factor eps * LAMBDA[l][|m|] that turns F' into
-// the log-visibility F is applied once per receiver by the exponential
-// kernel.
+//   F'_lm(x) = sum_i a_l(t_i) rho_l^|m|(s_z) T_m(s_x, s_y)
+// in registers, a_l and rho_l^m being the g_l and r_l^m of the basis whose
+// constants are left out (shv_device.h); the factor eps * PAIR[l][|m|] that
+// turns F' into the log-visibility F is applied once per receiver by the
+// exponential kernel.
 //
 // Backward: per pair the terms are recomputed (nothing per pair is stored).
 // With W_lm = dLoss/dF'_lm:
-//   dLoss/dt  = 2 pi sum_lm W_lm P_l(t) r_l^|m| T_m         (g_l' = 2 pi P_l)
-//   dLoss/ds  = grad of sum_lm W_lm g_l r_l^|m| T_m, projected on the tangent
+//   dLoss/dt  = -sum_lm W_lm (l + 1) p_l(t) rho_l^|m| T_m   (p_l: monic P_l)
+//   dLoss/ds  = grad of sum_lm W_lm a_l rho_l^|m| T_m, projected on the tangent
 //   plane, then chained through s = v/|v|, t = sqrt(1 - r^2/|v|^2), v = c - x.
 // Receiver gradients stay in registers; a sphere's four gradient values are
 // summed over the wave together (a transposed reduction: DPP moves and
@@ -27,6 +28,13 @@
 // order.  The block's chunk of sphere records is staged in LDS once and read
 // back as wave-uniform broadcasts (measured faster than scalar loads of each
 // record: pair adjoint 748 -> 703 us at 8 bands on the 64-scene batch).
+//
+// Bound: FP32 issue.  At 8 bands a pair takes 173 instructions forward and 368
+// backward (206 and 426 with recurrences along l and the Bonnet recurrence of
+// the cap).  The 64-scene batch, before and after, us: forward 292 -> 250 at 8
+// bands, 297 -> 243 at 6, 159 -> 135 at 4; adjoint 672 -> 566, 669 -> 559,
+// 372 -> 284.  Four waves per SIMD in the 8-band adjoint (128 registers
+// instead of 148) spill in the loop: 604 us.
 
 #pragma once
 
@@ -41,7 +49,8 @@ struct PairGeom {
   float inv;      // 1 / |c - x| (0 for a sphere centred on the receiver)
   float rs;       // r / |c - x|
   float t;        // cos(alpha), 0 when the receiver is inside the sphere
-  float u;        // 1 - t, formed as s^2 / (1 + t) so small caps keep their digits
+  float s2;       // 1 - t^2 = rs^2, 1 inside
+  float u;        // 1 - t, formed as s2 / (1 + t) so small caps keep their digits
 };
 
 __device__ __forceinline__ PairGeom pair_geom(float px, float py, float pz, float4 q) {
@@ -54,7 +63,8 @@ __device__ __forceinline__ PairGeom pair_geom(float px, float py, float pz, floa
   g.z = vz * g.inv;
   g.rs = q.w * g.inv;
   g.t = fast_sqrt(fmaxf(fmaf(-g.rs, g.rs, 1.0f), 0.0f));
-  g.u = fminf(g.rs * g.rs * fast_rcp(1.0f + g.t), 1.0f);  // = 1 when inside (t = 0)
+  g.s2 = fminf(g.rs * g.rs, 1.0f);
+  g.u = g.s2 * fast_rcp(1.0f + g.t);  // = 1 when inside (t = 0)
   return g;
 }
 
@@ -105,35 +115,26 @@ __device__ __forceinline__ void pair_fwd_item(const float* __restrict__ pts, int
   __syncthreads();
   for (int s = s0 + wave; s < s1; s += SHV_WAVES_PER_BLOCK) {
     const PairGeom G = pair_geom(px, py, pz, sh.sph[s - s0]);
-    float R[NB + 1], g[NB], C[NB], Sn[NB];
-    legendre_resid<NB>(G.t, G.u, R);
-    cap_zonal<NB>(G.u, R, g);
+    float g[NB], C[NB], Sn[NB], r[2][NB];
+    cap_terms<NB>(G.t, G.u, G.s2, g);
     cs_powers<NB>(G.x, G.y, C, Sn);
+    legendre_monic<NB>(G.z, r[0]);
+    {
+      const float y = g[0] - dc_comp;
+      const float t = acc[0] + y;
+      dc_comp = (t - acc[0]) - y;
+      acc[0] = t;
+    }
 #pragma unroll
-    for (int m = 0; m < NB; ++m) {
-      float r2 = 0.0f, r1 = 1.0f;
+    for (int l = 1; l < NB; ++l) acc[idx(l, 0)] = fmaf(g[l], r[0][l], acc[idx(l, 0)]);
+#pragma unroll
+    for (int m = 1; m < NB; ++m) {
+      legendre_row<NB>(m, G.z, r[(m - 1) & 1], r[m & 1]);
 #pragma unroll
       for (int l = m; l < NB; ++l) {
-        float u;
-        if (l == m) {
-          u = g[l];
-        } else {
-          const float r = (l == m + 1) ? G.z : fmaf(G.z, r1, SHV_GAMMA[l][m] * r2);
-          r2 = r1;
-          r1 = r;
-          u = g[l] * r;
-        }
-        if (m == 0 && l == 0) {
-          const float y = u - dc_comp;
-          const float t = acc[0] + y;
-          dc_comp = (t - acc[0]) - y;
-          acc[0] = t;
-        } else if (m == 0) {
-          acc[idx(l, 0)] += u;
-        } else {
-          acc[idx(l, m)] = fmaf(u, C[m], acc[idx(l, m)]);
-          acc[idx(l, -m)] = fmaf(u, Sn[m], acc[idx(l, -m)]);
-        }
+        const float u = l == m ? g[l] : g[l] * r[m & 1][l];
+        acc[idx(l, m)] = fmaf(u, C[m], acc[idx(l, m)]);
+        acc[idx(l, -m)] = fmaf(u, Sn[m], acc[idx(l, -m)]);
       }
     }
   }
@@ -181,49 +182,63 @@ struct PairBwdShared {
 };
 
 // Adjoint of one pair's term for the weights W_lm = dLoss/dF'_lm (and
-// Wz_lm = RHO[l][|m|] W_lm): the cotangent of v = c - x (gvx, gvy, gvz) and
-// of the radius (gr).
+// W0_l = ROW_0[l] W_l0, the weights of d p_l / dz in terms of rho_l^1): the
+// cotangent of v = c - x (gvx, gvy, gvz) and of the radius (gr).
+//
+// With b_lm = W_lm C_m + W_l,-m S_m, the degrees' sums f_l = sum_m rho_l^m b_lm
+// give dLoss/dt and h_l = sum_m (d rho_l^m / dz) b_lm the z derivative: one
+// instruction each per term where separate sums over l for every order and
+// both of cosine and sine took two, and no second set of weights.
 template <int NB>
-__device__ __forceinline__ void pair_adjoint(const PairGeom& G, const float (&W)[NB * NB], const float (&Wz)[NB * NB],
+__device__ __forceinline__ void pair_adjoint(const PairGeom& G, const float (&W)[NB * NB], const float (&W0)[NB],
                                              float& gvx, float& gvy, float& gvz, float& gr) {
-  float R[NB + 1], g[NB], C[NB], Sn[NB];
-  legendre_resid<NB>(G.t, G.u, R);
-  cap_zonal<NB>(G.u, R, g);
+  float g[NB], C[NB], Sn[NB], r[2][NB], f[NB], h[NB];
+  cap_terms<NB>(G.t, G.u, G.s2, g);
   cs_powers<NB>(G.x, G.y, C, Sn);
-  float Gx = 0.0f, Gy = 0.0f, Gz = 0.0f, Gt = 0.0f;
+  legendre_monic<NB>(G.z, r[0]);
+  if constexpr (NB > 1) legendre_row<NB>(1, G.z, r[0], r[1]);
+  f[0] = W[0];
 #pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    float Xc = 0.0f, Xs = 0.0f, Tc = 0.0f, Ts = 0.0f, Zc = 0.0f, Zs = 0.0f;
-    float r2 = 0.0f, r1 = 1.0f;
+  for (int l = 1; l < NB; ++l) {
+    f[l] = W[idx(l, 0)] * r[0][l];
+    h[l] = l == 1 ? W0[1] : W0[l] * r[1][l];
+  }
+  float Gx = 0.0f, Gy = 0.0f, Gz = 0.0f;
+#pragma unroll
+  for (int m = 1; m < NB; ++m) {
+    const float(&rm)[NB] = r[m & 1];
+    float(&rn)[NB] = r[(m + 1) & 1];
+    legendre_row<NB>(m + 1, G.z, rm, rn);
+    float Xc = 0.0f, Xs = 0.0f;
 #pragma unroll
     for (int l = m; l < NB; ++l) {
-      float r;
-      if (l == m) r = 1.0f;
-      else if (l == m + 1) r = G.z;
-      else r = fmaf(G.z, r1, SHV_GAMMA[l][m] * r2);
-      if (l > m) { r2 = r1; r1 = r; }
-      const float v = g[l] * r;   // value weight of r_l^m
-      const float w = fmaf(-R[l], r, r);  // P_l(t) r: t-derivative weight (times 1 / 2 pi)
-      if (m == 0) {
-        Tc = fmaf(W[idx(l, 0)], w, Tc);
-      } else {
-        Xc = fmaf(W[idx(l, m)], v, Xc);
-        Xs = fmaf(W[idx(l, -m)], v, Xs);
-        Tc = fmaf(W[idx(l, m)], w, Tc);
-        Ts = fmaf(W[idx(l, -m)], w, Ts);
-        Zc = fmaf(Wz[idx(l, m - 1)], v, Zc);
-        if (m - 1 >= 1) Zs = fmaf(Wz[idx(l, -(m - 1))], v, Zs);
-      }
+      const float wc = W[idx(l, m)], ws = W[idx(l, -m)];
+      const float b = fmaf(ws, Sn[m], wc * C[m]);
+      f[l] = l == m ? f[l] + b : fmaf(rm[l], b, f[l]);
+      if (l == m + 1) h[l] += b;
+      else if (l > m) h[l] = fmaf((l - m) & 1 ? rn[l] : SHV_ROW_K[m] * rn[l], b, h[l]);
+      const float v = l == m ? g[l] : g[l] * rm[l];
+      Xc = fmaf(wc, v, Xc);
+      Xs = fmaf(ws, v, Xs);
     }
-    Gt = fmaf(Tc, C[m], fmaf(Ts, Sn[m], Gt));
-    if (m >= 1) {
-      const float fm = (float)m;
-      Gz = fmaf(Zc, C[m - 1], fmaf(Zs, Sn[m - 1], Gz));
-      Gx = fmaf(fm, fmaf(Xc, C[m - 1], Xs * Sn[m - 1]), Gx);
-      Gy = fmaf(fm, fmaf(Xs, C[m - 1], -Xc * Sn[m - 1]), Gy);
+    const float fm = (float)m;
+    if (m == 1) {
+      Gx = Xc;
+      Gy = Xs;
+    } else {
+      const float mc = fm * C[m - 1], ms = fm * Sn[m - 1];
+      Gx = fmaf(Xc, mc, fmaf(Xs, ms, Gx));
+      Gy = fmaf(Xs, mc, fmaf(-Xc, ms, Gy));
     }
   }
-  Gt *= SHV_TWO_PI;
+  float p[NB];
+  legendre_monic<NB>(G.t, p);
+  float Gt = -f[0];  // d a_l / dt = -(l + 1) p_l
+#pragma unroll
+  for (int l = 1; l < NB; ++l) {
+    Gz = fmaf(g[l], h[l], Gz);
+    Gt = fmaf(-(float)(l + 1), p[l] * f[l], Gt);
+  }
   // chain rule: s = v/|v| (tangential part / |v|), t(|v|, r)
   const float sd = fmaf(Gx, G.x, fmaf(Gy, G.y, Gz * G.z));
   gvx = (Gx - sd * G.x) * G.inv;
@@ -258,18 +273,12 @@ __device__ __forceinline__ void pair_bwd_item(const float* __restrict__ Wg, cons
   const float py = sel0(ok, pts[P + q]);
   const float pz = sel0(ok, pts[2 * P + q]);
 
-  // W_lm and its z-derivative weights RHO[l][|m|] W_lm (zero on tail lanes,
-  // so they contribute nothing to the sphere sums).
-  float W[N], Wz[N];
+  // Zero on tail lanes, so they contribute nothing to the sphere sums.
+  float W[N], W0[NB];
 #pragma unroll
-  for (int l = 0; l < NB; ++l) {
+  for (int i = 0; i < N; ++i) W[i] = sel0(ok, Wg[(int64_t)i * P + q]);
 #pragma unroll
-    for (int m = -l; m <= l; ++m) {
-      const float w = sel0(ok, Wg[(int64_t)idx(l, m) * P + q]);
-      W[idx(l, m)] = w;
-      Wz[idx(l, m)] = w * SHV_RHO[l][m < 0 ? -m : m];
-    }
-  }
+  for (int l = 0; l < NB; ++l) W0[l] = W[idx(l, 0)] * SHV_ROW_0[l];
 
   float gpx = 0.0f, gpy = 0.0f, gpz = 0.0f;
   for (int j = threadIdx.x; j < s1 - s0; j += SHV_BLOCK) sh.sph[j] = sph[s0 + j];
@@ -277,7 +286,7 @@ __device__ __forceinline__ void pair_bwd_item(const float* __restrict__ Wg, cons
   for (int s = s0 + wave; s < s1; s += SHV_WAVES_PER_BLOCK) {
     const PairGeom G = pair_geom(px, py, pz, sh.sph[s - s0]);
     float gvx, gvy, gvz, gr;
-    pair_adjoint<NB>(G, W, Wz, gvx, gvy, gvz, gr);
+    pair_adjoint<NB>(G, W, W0, gvx, gvy, gvz, gr);
     gpx -= gvx;
     gpy -= gvy;
     gpz -= gvz;

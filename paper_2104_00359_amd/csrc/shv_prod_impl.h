@@ -42,33 +42,25 @@
 
 namespace shv {
 
-// h = LAMBDA (.) F' of one pair: the same recurrence and products as the pair
-// forward kernel, each coefficient scaled by its LAMBDA[l][|m|].
+// h = PAIR (.) F' of one pair: the same rows and products as the pair forward
+// kernel, each coefficient scaled by its PAIR[l][|m|].
 template <int NB>
 __device__ __forceinline__ void blocker_vec(const PairGeom& G, float (&h)[NB * NB]) {
-  float R[NB + 1], g[NB], C[NB], Sn[NB];
-  legendre_resid<NB>(G.t, G.u, R);
-  cap_zonal<NB>(G.u, R, g);
+  float g[NB], C[NB], Sn[NB], r[2][NB];
+  cap_terms<NB>(G.t, G.u, G.s2, g);
   cs_powers<NB>(G.x, G.y, C, Sn);
+  legendre_monic<NB>(G.z, r[0]);
 #pragma unroll
   for (int m = 0; m < NB; ++m) {
-    float r2 = 0.0f, r1 = 1.0f;
+    if (m >= 1) legendre_row<NB>(m, G.z, r[(m - 1) & 1], r[m & 1]);
 #pragma unroll
     for (int l = m; l < NB; ++l) {
-      float u;
-      if (l == m) {
-        u = g[l];
-      } else {
-        const float r = (l == m + 1) ? G.z : fmaf(G.z, r1, SHV_GAMMA[l][m] * r2);
-        r2 = r1;
-        r1 = r;
-        u = g[l] * r;
-      }
+      const float u = l == m ? g[l] : g[l] * r[m & 1][l];
       if (m == 0) {
-        h[idx(l, 0)] = SHV_LAMBDA[l][0] * u;
+        h[idx(l, 0)] = SHV_PAIR[l][0] * u;
       } else {
-        h[idx(l, m)] = SHV_LAMBDA[l][m] * (u * C[m]);
-        h[idx(l, -m)] = SHV_LAMBDA[l][m] * (u * Sn[m]);
+        h[idx(l, m)] = SHV_PAIR[l][m] * (u * C[m]);
+        h[idx(l, -m)] = SHV_PAIR[l][m] * (u * Sn[m]);
       }
     }
   }
@@ -186,19 +178,19 @@ __device__ __forceinline__ void prod_bwd_group(ProdBwdShared<NB>& sh, int lane, 
     {
       // This wave's share of the pair weights: W_lm = LAMBDA_lm hbar_lm on
       // its output group, 0 elsewhere (the pair adjoint is linear in W).
-      float W[N], Wz[N];
+      float W[N], W0[NB];
 #pragma unroll
       for (int l = 0; l < NB; ++l) {
 #pragma unroll
         for (int m = -l; m <= l; ++m) {
           const int i = idx(l, m);
-          const float w = group_of<NB>(i) == G ? SHV_LAMBDA[l][m < 0 ? -m : m] * (hbeta * T[i]) : 0.0f;
+          const float w = group_of<NB>(i) == G ? SHV_PAIR[l][m < 0 ? -m : m] * (hbeta * T[i]) : 0.0f;
           W[i] = w;
-          Wz[i] = w * SHV_RHO[l][m < 0 ? -m : m];
+          if (m == 0) W0[l] = w * SHV_ROW_0[l];
         }
       }
       float gvx, gvy, gvz, gr;
-      pair_adjoint<NB>(geo, W, Wz, gvx, gvy, gvz, gr);
+      pair_adjoint<NB>(geo, W, W0, gvx, gvy, gvz, gr);
       gpx -= gvx;
       gpy -= gvy;
       gpz -= gvz;

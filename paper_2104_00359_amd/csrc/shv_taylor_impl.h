@@ -133,7 +133,7 @@ __global__ __launch_bounds__(SHV_BLOCK) void k_exp_taylor_fwd(const float* __res
   }
 }
 
-// Writes W_i = eps LAMBDA_i dLoss/dF_i, the weights of the pair adjoint.
+// Writes W_i = eps PAIR_i dLoss/dF_i, the weights of the pair adjoint.
 template <int NB, int G>
 __device__ __forceinline__ void taylor_bwd_group(TaylorShared<NB>& sh, int lane, int64_t p, bool ok,
                                                  const float* __restrict__ gIn, const float* __restrict__ vis,
@@ -224,7 +224,7 @@ __device__ __forceinline__ void taylor_bwd_group(TaylorShared<NB>& sh, int lane,
     for (int m = -l; m <= l; ++m) {
       const int i = idx(l, m);
       if (group_of<NB>(i) != G) continue;
-      const float lam = eps * (Lat<NB>::USE ? SHV_LAT_LAMI : SHV_LAMBDA)[l][m < 0 ? -m : m];
+      const float lam = eps * (Lat<NB>::USE ? SHV_LAT_LAMI : SHV_PAIR)[l][m < 0 ? -m : m];
       Wout[(int64_t)i * P + p] = i == 0 ? lam * (cbar * SHV_INV_SQRT_4PI) : lam * (scale * Gb[i]);
     }
   }
