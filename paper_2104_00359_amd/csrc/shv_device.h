@@ -85,12 +85,21 @@ __device__ __forceinline__ void legendre_monic(float z, float (&r)[NB]) {
     r[l] = l == 2 ? fmaf(z, z, -SHV_LEG_B[1]) : fmaf(z, r[l - 1], -SHV_LEG_B[l - 1] * r[l - 2]);
 }
 
-// rho_l^m, m <= l < NB, from rho_l^{m-1} (m = 1: from p_l).
+// rho_l^m, m <= l < NB, from rho_l^{m-1} (m = 1: from p_l).  one = 1 (vector_one()).
 template <int NB>
-__device__ __forceinline__ void legendre_row(int m, float z, const float (&below)[NB], float (&r)[NB]) {
+__device__ __forceinline__ void legendre_row(int m, float z, float one, const float (&below)[NB], float (&r)[NB]) {
 #pragma unroll
   for (int l = m; l < NB; ++l)
-    r[l] = l == m ? 1.0f : l == m + 1 ? z : fmaf(SHV_ROW[l][m], below[l - 1], r[l - 2]);
+    r[l] = l == m ? 1.0f : l == m + 1 ? z : fmaf(SHV_ROW[l][m], below[l - 1], l == m + 2 ? one : r[l - 2]);
+}
+
+// 1.0 in a vector register: with it as the addend the constant factor of a
+// multiply-add is a literal; with the inline constant it would be a scalar
+// register, which issues at half rate.
+__device__ __forceinline__ float vector_one() {
+  float one = 1.0f;
+  asm("" : "+v"(one));
+  return one;
 }
 
 // a_l(t): a_0 = u = 1 - t and a_l = s2 times the monic P_l'(t), s2 = 1 - t^2.
@@ -197,44 +206,31 @@ __device__ __forceinline__ float wave_sum_last(float v) {
   return v;
 }
 
-// The value of v in the lane that DPP control CTRL selects (0 where that lane
-// lies outside the row).
+// v[l] + v[l - N] in a row (0 from outside it).
 template <int CTRL>
-__device__ __forceinline__ float dpp_from(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+__device__ __forceinline__ float row_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
-// v[l] + v[l ^ 16] and v[l] + v[l ^ 32] in every lane l, by gfx950's
-// permlane swaps of v with itself (the two results hold v[l] and its partner
-// in some order; the sum is the same bits either way).
-__device__ __forceinline__ float xor16_add(float v) {
-  const int i = __float_as_int(v);
-  const auto r = __builtin_amdgcn_permlane16_swap(i, i, false, false);
+// Totals over the wave of four per-lane values, transposed: lane 15 of row r
+// (lanes 16 r .. 16 r + 15) returns the total of value r.  A swap of halves (of
+// odd and even rows) puts two values side by side, one addition halves both:
+// no selects, which issue at half rate.  Then each row sums its own value.  A
+// fixed order of additions, 10 instructions.
+__device__ __forceinline__ float swap32_add(float a, float b) {  // lanes < 32: a[l] + a[l + 32], else of b
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
   return __int_as_float(r[0]) + __int_as_float(r[1]);
 }
-__device__ __forceinline__ float xor32_add(float v) {
-  const int i = __float_as_int(v);
-  const auto r = __builtin_amdgcn_permlane32_swap(i, i, false, false);
+__device__ __forceinline__ float swap16_add(float a, float b) {  // even rows: a[l] + a[l + 16], odd rows of b
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
   return __int_as_float(r[0]) + __int_as_float(r[1]);
 }
-
-// Totals over the wave of four per-lane values, transposed: lane l returns
-// the total of value (l & 3) (a, b, c, d in that order), complete in lanes
-// 12..15 of every row (so in lanes 60..63).  Lanes l and l ^ 1 first split the
-// four values between them (even lanes keep a and c), lanes l and l ^ 2 then
-// split the two sums, so each lane carries one value from there on: quads of a
-// row by row_shr 4 and 8, rows by the xor-16 and xor-32 swaps.  A fixed order
-// of additions, about 17 instructions for the four sums.
 __device__ __forceinline__ float wave_sum4(float a, float b, float c, float d) {
-  const int lane = threadIdx.x & 63;
-  const bool odd = (lane & 1) != 0, hi = (lane & 2) != 0;
-  const float u = (odd ? b : a) + dpp_from<0xB1>(odd ? a : b);  // quad_perm [1,0,3,2]: lane l ^ 1
-  const float v = (odd ? d : c) + dpp_from<0xB1>(odd ? c : d);
-  float w = (hi ? v : u) + dpp_from<0x4E>(hi ? u : v);           // quad_perm [2,3,0,1]: lane l ^ 2
-  w += dpp_from<0x114>(w);                                        // row_shr:4
-  w += dpp_from<0x118>(w);                                        // row_shr:8
-  w = xor16_add(w);
-  return xor32_add(w);
+  float v = swap16_add(swap32_add(a, c), swap32_add(b, d));
+  v = row_add<0x111>(v);  // row_shr:1
+  v = row_add<0x112>(v);
+  v = row_add<0x114>(v);
+  return row_add<0x118>(v);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {

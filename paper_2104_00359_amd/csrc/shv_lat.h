@@ -182,10 +182,11 @@ __device__ __forceinline__ void lat_mul(const float (&A)[NB], const float (&B)[N
   }
 }
 
-// One row of a product: o += its share, for the orders of group G.  SQUARE:
+// One row of a product: o += its share (o = its share for the first row), for
+// the orders of group G.  SQUARE:
 // (e - mean)^2, else twice (e - mean) h.
 template <int NB, int G, bool SQUARE, bool EQ, class Coef>
-__device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const float* __restrict__ Q,
+__device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const float* __restrict__ Q, bool first,
                                         float (&o)[NB * NB]) {
   float A[2][NB], B[2][NB], X[2][NB], Y[2][NB];
   lat_up<NB, EQ, false>(e, Q, A, B);
@@ -206,8 +207,9 @@ __device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const
       const bool odd = ((l - m) & 1) != 0;
       if (EQ && odd) continue;
       const float t = Q[lat_at<NB>(m) + l - m];
-      o[idx(l, m)] = fmaf(t, odd ? oa : ea, o[idx(l, m)]);
-      if (m > 0) o[idx(l, -m)] = fmaf(t, odd ? ob : eb, o[idx(l, -m)]);
+      const float va = odd ? oa : ea, vb = odd ? ob : eb;
+      o[idx(l, m)] = first ? t * va : fmaf(t, va, o[idx(l, m)]);
+      if (m > 0) o[idx(l, -m)] = first ? t * vb : fmaf(t, vb, o[idx(l, -m)]);
     }
   }
 }
@@ -217,18 +219,15 @@ __device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const
 template <int NB, int G, bool SQUARE, class Coef, class Between>
 __device__ __forceinline__ void lat_product(Coef e, const float (&h)[NB * NB], float (&o)[NB * NB], Between between) {
   constexpr int N = NB * NB, QP = Lat<NB>::QP;
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    if (G < 0 || group_of<NB>(i) == G) o[i] = 0.0f;
   const float* __restrict__ Q = LatTab<NB>::rows();
 #pragma unroll
   for (int t = 0; t < LatTab<NB>::PAIRS; ++t) {
     between();
-    lat_row<NB, G, SQUARE, false>(e, h, Q + t * QP, o);
+    lat_row<NB, G, SQUARE, false>(e, h, Q + t * QP, t == 0, o);
   }
   if constexpr (LatTab<NB>::EQ > 0) {
     between();
-    lat_row<NB, G, SQUARE, true>(e, h, Q + LatTab<NB>::PAIRS * QP, o);
+    lat_row<NB, G, SQUARE, true>(e, h, Q + LatTab<NB>::PAIRS * QP, false, o);
   }
   const float t0 = 2.0f * e(0);
 #pragma unroll

@@ -29,12 +29,16 @@
 // back as wave-uniform broadcasts (measured faster than scalar loads of each
 // record: pair adjoint 748 -> 703 us at 8 bands on the 64-scene batch).
 //
-// Bound: FP32 issue.  At 8 bands a pair takes 173 instructions forward and 368
-// backward (206 and 426 with recurrences along l and the Bonnet recurrence of
-// the cap).  The 64-scene batch, before and after, us: forward 292 -> 250 at 8
-// bands, 297 -> 243 at 6, 159 -> 135 at 4; adjoint 672 -> 566, 669 -> 559,
-// 372 -> 284.  Four waves per SIMD in the 8-band adjoint (128 registers
-// instead of 148) spill in the loop: 604 us.
+// Bound: FP32 issue, and in launches of 100 us and more the clock that the card
+// holds under it (2.05 GHz of 2.4).  At 8 bands a pair takes 172 instructions
+// forward and 390 backward, its sums over the wave included (206 and 443 with
+// recurrences along l and the Bonnet recurrence of the cap).  Multiply-adds
+// with a scalar operand, selects, compares, minima and maxima issue at half
+// rate and reciprocals and roots at a quarter, so the loops hold constants as
+// literals, clamp by modifier, and form 1 - t without a division.  The 64-scene
+// batch, before and after, us, the fastest of twenty launches: forward 276 -> 222
+// at 8 bands, 279 -> 219 at 6, 149 -> 115 at 4; adjoint 627 -> 485, 620 -> 490,
+// 343 -> 262.
 
 #pragma once
 
@@ -48,9 +52,9 @@ struct PairGeom {
   float x, y, z;  // unit direction receiver -> centre
   float inv;      // 1 / |c - x| (0 for a sphere centred on the receiver)
   float rs;       // r / |c - x|
-  float t;        // cos(alpha), 0 when the receiver is inside the sphere
-  float s2;       // 1 - t^2 = rs^2, 1 inside
-  float u;        // 1 - t, formed as s2 / (1 + t) so small caps keep their digits
+  float s2, t2;   // sin^2 and cos^2 of alpha: rs^2 and 1 - rs^2; 1 and 0 when the receiver is inside the sphere
+  float t;        // cos(alpha)
+  float u;        // 1 - t
 };
 
 __device__ __forceinline__ PairGeom pair_geom(float px, float py, float pz, float4 q) {
@@ -62,9 +66,13 @@ __device__ __forceinline__ PairGeom pair_geom(float px, float py, float pz, floa
   g.y = vy * g.inv;
   g.z = vz * g.inv;
   g.rs = q.w * g.inv;
-  g.t = fast_sqrt(fmaxf(fmaf(-g.rs, g.rs, 1.0f), 0.0f));
   g.s2 = fminf(g.rs * g.rs, 1.0f);
-  g.u = g.s2 * fast_rcp(1.0f + g.t);  // = 1 when inside (t = 0)
+  g.t2 = __builtin_amdgcn_fmed3f(fmaf(-g.rs, g.rs, 1.0f), 0.0f, 1.0f);
+  g.t = fast_sqrt(g.t2);
+  // u solves u^2 - 2 u + s2 = 0; from u = 1 - t, whose error is one of t, the
+  // step leaves u times that error: small caps keep their digits.
+  const float u = 1.0f - g.t;
+  g.u = 0.5f * fmaf(u, u, g.s2);  // = 1 when inside (t = 0)
   return g;
 }
 
@@ -113,6 +121,7 @@ __device__ __forceinline__ void pair_fwd_item(const float* __restrict__ pts, int
 
   for (int j = threadIdx.x; j < s1 - s0; j += SHV_BLOCK) sh.sph[j] = sph[s0 + j];
   __syncthreads();
+  const float one = vector_one();
   for (int s = s0 + wave; s < s1; s += SHV_WAVES_PER_BLOCK) {
     const PairGeom G = pair_geom(px, py, pz, sh.sph[s - s0]);
     float g[NB], C[NB], Sn[NB], r[2][NB];
@@ -129,7 +138,7 @@ __device__ __forceinline__ void pair_fwd_item(const float* __restrict__ pts, int
     for (int l = 1; l < NB; ++l) acc[idx(l, 0)] = fmaf(g[l], r[0][l], acc[idx(l, 0)]);
 #pragma unroll
     for (int m = 1; m < NB; ++m) {
-      legendre_row<NB>(m, G.z, r[(m - 1) & 1], r[m & 1]);
+      legendre_row<NB>(m, G.z, one, r[(m - 1) & 1], r[m & 1]);
 #pragma unroll
       for (int l = m; l < NB; ++l) {
         const float u = l == m ? g[l] : g[l] * r[m & 1][l];
@@ -181,6 +190,13 @@ struct PairBwdShared {
   float gpx_w[SHV_WAVES_PER_BLOCK - 1][3][64];
 };
 
+// v, computed here: a select between v and a constant does not become a branch
+// around v's computation, which would split the loop body.
+__device__ __forceinline__ float here(float v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // Adjoint of one pair's term for the weights W_lm = dLoss/dF'_lm (and
 // W0_l = ROW_0[l] W_l0, the weights of d p_l / dz in terms of rho_l^1): the
 // cotangent of v = c - x (gvx, gvy, gvz) and of the radius (gr).
@@ -189,14 +205,22 @@ struct PairBwdShared {
 // give dLoss/dt and h_l = sum_m (d rho_l^m / dz) b_lm the z derivative: one
 // instruction each per term where separate sums over l for every order and
 // both of cosine and sine took two, and no second set of weights.
+//
+// 1/t is wanted outside the sphere only.  A branch there is the faster form (64-scene
+// batch: 262 us against 282 with selects at 4 bands, 517 against 522 at 6), but at 8 bands
+// it splits the body, and the four waves per SIMD that 128 registers allow spill
+// (762 us against 510).
 template <int NB>
-__device__ __forceinline__ void pair_adjoint(const PairGeom& G, const float (&W)[NB * NB], const float (&W0)[NB],
-                                             float& gvx, float& gvy, float& gvz, float& gr) {
+__device__ __forceinline__ void pair_adjoint(const PairGeom& G, float one, const float (&W)[NB * NB],
+                                             const float (&W0)[NB], float& gvx, float& gvy, float& gvz, float& gr) {
+  constexpr bool SELECT = NB == 8;
   float g[NB], C[NB], Sn[NB], r[2][NB], f[NB], h[NB];
-  cap_terms<NB>(G.t, G.u, G.s2, g);
+  const float it = SELECT ? here(fast_rsqrt(G.t2)) : 0.0f;  // 1 / t
+  const float t = !SELECT ? G.t : G.t2 > 0.0f ? G.t2 * it : 0.0f;
+  cap_terms<NB>(t, G.u, G.s2, g);
   cs_powers<NB>(G.x, G.y, C, Sn);
   legendre_monic<NB>(G.z, r[0]);
-  if constexpr (NB > 1) legendre_row<NB>(1, G.z, r[0], r[1]);
+  if constexpr (NB > 1) legendre_row<NB>(1, G.z, one, r[0], r[1]);
   f[0] = W[0];
 #pragma unroll
   for (int l = 1; l < NB; ++l) {
@@ -208,7 +232,7 @@ __device__ __forceinline__ void pair_adjoint(const PairGeom& G, const float (&W)
   for (int m = 1; m < NB; ++m) {
     const float(&rm)[NB] = r[m & 1];
     float(&rn)[NB] = r[(m + 1) & 1];
-    legendre_row<NB>(m + 1, G.z, rm, rn);
+    legendre_row<NB>(m + 1, G.z, one, rm, rn);
     float Xc = 0.0f, Xs = 0.0f;
 #pragma unroll
     for (int l = m; l < NB; ++l) {
@@ -232,7 +256,7 @@ __device__ __forceinline__ void pair_adjoint(const PairGeom& G, const float (&W)
     }
   }
   float p[NB];
-  legendre_monic<NB>(G.t, p);
+  legendre_monic<NB>(t, p);
   float Gt = -f[0];  // d a_l / dt = -(l + 1) p_l
 #pragma unroll
   for (int l = 1; l < NB; ++l) {
@@ -244,15 +268,19 @@ __device__ __forceinline__ void pair_adjoint(const PairGeom& G, const float (&W)
   gvx = (Gx - sd * G.x) * G.inv;
   gvy = (Gy - sd * G.y) * G.inv;
   gvz = (Gz - sd * G.z) * G.inv;
-  gr = 0.0f;
-  if (G.t > 0.0f) {
-    const float k = Gt * G.rs * fast_rcp(G.t) * G.inv;  // dLoss/dt * (-dt/dr); t > 0 here
-    const float kd = k * G.rs;                // dLoss/dt * dt/d|v|
-    gvx = fmaf(kd, G.x, gvx);
-    gvy = fmaf(kd, G.y, gvy);
-    gvz = fmaf(kd, G.z, gvz);
-    gr = -k;
+  // dLoss/dt * (-dt/dr); a receiver inside the sphere (t = 0) has none
+  float k = 0.0f;
+  if constexpr (SELECT) {
+    const float ks = here((Gt * G.rs) * (it * G.inv));
+    k = G.t2 > 0.0f ? ks : 0.0f;
+  } else if (G.t > 0.0f) {
+    k = (Gt * G.rs) * (fast_rcp(G.t) * G.inv);
   }
+  const float kd = k * G.rs;  // dLoss/dt * dt/d|v|
+  gvx = fmaf(kd, G.x, gvx);
+  gvy = fmaf(kd, G.y, gvy);
+  gvz = fmaf(kd, G.z, gvz);
+  gr = -k;
 }
 
 template <int NB>
@@ -283,15 +311,16 @@ __device__ __forceinline__ void pair_bwd_item(const float* __restrict__ Wg, cons
   float gpx = 0.0f, gpy = 0.0f, gpz = 0.0f;
   for (int j = threadIdx.x; j < s1 - s0; j += SHV_BLOCK) sh.sph[j] = sph[s0 + j];
   __syncthreads();
+  const float one = vector_one();
   for (int s = s0 + wave; s < s1; s += SHV_WAVES_PER_BLOCK) {
     const PairGeom G = pair_geom(px, py, pz, sh.sph[s - s0]);
     float gvx, gvy, gvz, gr;
-    pair_adjoint<NB>(G, W, W0, gvx, gvy, gvz, gr);
+    pair_adjoint<NB>(G, one, W, W0, gvx, gvy, gvz, gr);
     gpx -= gvx;
     gpy -= gvy;
     gpz -= gvz;
-    const float tot = wave_sum4(gvx, gvy, gvz, gr);  // total of (gvx, gvy, gvz, gr)[lane & 3]
-    if (lane >= 60) reinterpret_cast<float*>(red)[(s - s0) * 4 + (lane & 3)] = tot;  // one wave per sphere
+    const float tot = wave_sum4(gvx, gvy, gvz, gr);  // total of (gvx, gvy, gvz, gr)[lane / 16]
+    if ((lane & 15) == 15) reinterpret_cast<float*>(red)[(s - s0) * 4 + (lane >> 4)] = tot;  // one wave per sphere
   }
   if (wave > 0) {
     gpx_w[wave - 1][0][lane] = gpx;
@@ -315,7 +344,7 @@ __device__ __forceinline__ void pair_bwd_item(const float* __restrict__ Wg, cons
 }
 
 template <int NB>
-__global__ __launch_bounds__(SHV_BLOCK) void k_pair_bwd(const float* __restrict__ Wg, const float* __restrict__ pts,
+__global__ __launch_bounds__(SHV_BLOCK, NB == 8 ? 4 : 1) void k_pair_bwd(const float* __restrict__ Wg, const float* __restrict__ pts,
                                                         int64_t P, const float4* __restrict__ sph, int S, int chunk,
                                                         float* __restrict__ gp_part, float4* __restrict__ gs_part) {
   __shared__ PairBwdShared sh;
@@ -357,7 +386,7 @@ __global__ __launch_bounds__(SHV_BLOCK) void k_batch_pair_fwd(const char* __rest
 }
 
 template <int NB>
-__global__ __launch_bounds__(SHV_BLOCK) void k_batch_pair_bwd(const char* __restrict__ table) {
+__global__ __launch_bounds__(SHV_BLOCK, NB == 8 ? 4 : 1) void k_batch_pair_bwd(const char* __restrict__ table) {
   __shared__ PairBwdShared sh;
   const BatchView v(table);
   const int64_t item = blockIdx.x;

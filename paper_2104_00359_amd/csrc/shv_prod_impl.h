@@ -52,7 +52,7 @@ __device__ __forceinline__ void blocker_vec(const PairGeom& G, float (&h)[NB * N
   legendre_monic<NB>(G.z, r[0]);
 #pragma unroll
   for (int m = 0; m < NB; ++m) {
-    if (m >= 1) legendre_row<NB>(m, G.z, r[(m - 1) & 1], r[m & 1]);
+    if (m >= 1) legendre_row<NB>(m, G.z, 1.0f, r[(m - 1) & 1], r[m & 1]);
 #pragma unroll
     for (int l = m; l < NB; ++l) {
       const float u = l == m ? g[l] : g[l] * r[m & 1][l];
@@ -190,7 +190,7 @@ __device__ __forceinline__ void prod_bwd_group(ProdBwdShared<NB>& sh, int lane, 
         }
       }
       float gvx, gvy, gvz, gr;
-      pair_adjoint<NB>(geo, W, W0, gvx, gvy, gvz, gr);
+      pair_adjoint<NB>(geo, 1.0f, W, W0, gvx, gvy, gvz, gr);
       gpx -= gvx;
       gpy -= gvy;
       gpz -= gvz;
@@ -684,7 +684,7 @@ __device__ __forceinline__ void turn_bwd_wave(TurnBwdShared<NB>& sh, int lane, i
     gpy -= gvy;
     gpz -= gvz;
     const float tot = wave_sum4(gvx, gvy, gvz, gr);
-    if (lane >= 60) reinterpret_cast<float*>(gs_row + s)[lane & 3] = tot;
+    if ((lane & 15) == 15) reinterpret_cast<float*>(gs_row + s)[lane >> 4] = tot;
   }
   if (W > 0) {
     sh.gp[W - 1][0][lane] = gpx;
