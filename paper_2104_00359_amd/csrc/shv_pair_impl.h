@@ -88,7 +88,7 @@ struct PairFwdHalf {
 };
 template <int NB>
 union PairFwdShared {
-  float X[SHV_WAVES_PER_BLOCK - 1][PairFwdHalf<NB>::H][64];
+  float X[SHV_WAVES_PER_BLOCK][PairFwdHalf<NB>::H][64];
   float4 sph[SHV_MAX_CHUNK];
 };
 
@@ -148,24 +148,27 @@ __device__ __forceinline__ void pair_fwd_item(const float* __restrict__ pts, int
     }
   }
   // Coefficient i of the block is ((acc_0 + acc_1) + acc_2) + acc_3 over the
-  // waves, formed by wave 0 in two exchanges of half the coefficients.
+  // waves, in two exchanges of half the coefficients; each wave adds up every
+  // fourth coefficient.
   constexpr int H = PairFwdHalf<NB>::H;
+  const int w0 = __builtin_amdgcn_readfirstlane(wave);
   float* out = Fpart + (int64_t)by * N * P + p;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     __syncthreads();  // the spheres (h = 0) or the previous half (h = 1) are no longer read
-    if (wave > 0) {
 #pragma unroll
-      for (int i = h * H; i < N && i < (h + 1) * H; ++i) X[wave - 1][i - h * H][lane] = acc[i];
-    }
+    for (int i = h * H; i < N && i < (h + 1) * H; ++i) X[wave][i - h * H][lane] = acc[i];
     __syncthreads();
-    if (wave == 0 && ok) {
+    if (ok) {
 #pragma unroll
-      for (int i = h * H; i < N && i < (h + 1) * H; ++i) {
-        float v = acc[i];
+      for (int b = h * H; b < N && b < (h + 1) * H; b += SHV_WAVES_PER_BLOCK) {
+        const int i = b + w0;
+        if (i < N && i < (h + 1) * H) {
+          float v = X[0][i - h * H][lane];
 #pragma unroll
-        for (int w = 0; w < SHV_WAVES_PER_BLOCK - 1; ++w) v += X[w][i - h * H][lane];
-        out[(int64_t)i * P] = v;
+          for (int w = 1; w < SHV_WAVES_PER_BLOCK; ++w) v += X[w][i - h * H][lane];
+          out[(int64_t)i * P] = v;
+        }
       }
     }
   }
