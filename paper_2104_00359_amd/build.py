@@ -2,8 +2,10 @@
 
 Steps: generate the constant tables and unrolled SH-product code
 (csrc/gen_tables.py), compile each HIP translation unit to an object in
-parallel, link a shared library next to this file; also build the VALU
-issue-rate probe (csrc/valu_rate_probe.hip) next to it.
+parallel, link a shared library next to this file; compile the host side of the Python
+operations (csrc/shv_host.cpp, an extension module that calls the library by
+address); also build the VALU issue-rate probe (csrc/valu_rate_probe.hip) next
+to it.
 """
 from __future__ import annotations
 
@@ -17,6 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libshvis.so")
+HOST = os.path.join(HERE, "_host.so")
 # (source, extra flags, object name): the band-count-dependent kernels are
 # compiled once per band count.
 SOURCES = [("shv_nb.hip", [f"-DSHV_NB={n}", f"-DSHV_PART={part}"], f"shv_nb{n}_p{part}.o")
@@ -49,6 +52,22 @@ def _newest_input():
     return max(os.path.getmtime(n) for n in names)
 
 
+def build_host() -> None:
+    """The extension module of the Python operations (host code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    inc = [f"-I{d}" for d in (os.path.join(ROOT, "include"), CSRC, sysconfig.get_paths()["include"],
+                              "/opt/rocm/include")]
+    inc += [f"-isystem{d}" for d in cpp_extension.include_paths()]
+    _run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+          os.path.join(CSRC, "shv_host.cpp"), "-o", HOST + ".tmp",
+          *[f"-L{d}" for d in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    os.replace(HOST + ".tmp", HOST)
+
+
 def build(verbose: bool = False, jobs: int = 8, incremental: bool = False) -> str:
     """Compile everything (``incremental`` skips objects newer than every
     source and header; meant for development only)."""
@@ -73,7 +92,9 @@ def build(verbose: bool = False, jobs: int = 8, incremental: bool = False) -> st
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        host = ex.submit(build_host)
         objs = list(ex.map(compile_one, SOURCES))
+        host.result()
     tmp = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, LIB)

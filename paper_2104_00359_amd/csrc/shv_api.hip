@@ -17,6 +17,7 @@
 #include "shv_batch.h"
 #include "shv_config.h"
 #include "shv_launch.h"
+#include "shv_soa.h"
 
 namespace {
 
@@ -925,6 +926,13 @@ shv_status sh_l2_loss(const float* value, const float* target, int64_t n, float*
   SHV_TRY(need(loss, "loss"));
   SHV_TRY(check_ws(ws, ws_bytes, shv_l2_workspace_bytes(n)));
   return launch("l2_loss", stream, [&] { return shv::launch_l2(value, target, n, grad, (float*)ws, loss, stream); });
+}
+
+shv_status shv_internal_soa(const float* a, const float* b, int64_t P, float* oa, float* ob, hipStream_t stream) {
+  SHV_TRY(check_device());
+  SHV_TRY(check_sizes(P, 0));
+  if (P == 0) return SHV_OK;
+  return launch("soa", stream, [&] { return shv::launch_soa(a, b, P, oa, ob, stream); });
 }
 
 shv_status sh_sgd_step(float* x, const float* grad, int64_t n, float lr, hipStream_t stream) {

@@ -53,6 +53,24 @@ hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
+// [P][3] rows of two arrays -> [3][P], one receiver per lane (P > 0).
+__global__ __launch_bounds__(SHV_BLOCK) void k_soa(const float* __restrict__ a, const float* __restrict__ b, int64_t P,
+                                                   float* __restrict__ oa, float* __restrict__ ob) {
+  const int64_t p = (int64_t)blockIdx.x * SHV_BLOCK + threadIdx.x;
+  if (p >= P) return;
+  const float* __restrict__ in = blockIdx.y ? b : a;
+  float* __restrict__ out = blockIdx.y ? ob : oa;
+  const float x = in[3 * p], y = in[3 * p + 1], z = in[3 * p + 2];
+  out[p] = x;
+  out[P + p] = y;
+  out[2 * P + p] = z;
+}
+
+hipError_t launch_soa(const float* a, const float* b, int64_t P, float* oa, float* ob, hipStream_t st) {
+  k_soa<<<dim3((unsigned)point_blocks(P), 2), SHV_BLOCK, 0, st>>>(a, b, P, oa, ob);
+  return hipGetLastError();
+}
+
 // out[j] = sum_c part[c * len + j], c in order.
 __device__ __forceinline__ void sum_chunks_at(const float* __restrict__ part, int nchunks, int64_t len, int64_t j,
                                               float* __restrict__ out) {

@@ -197,6 +197,7 @@ hipError_t launch_deform_backward(const DeformGraphDev& g, const float* params, 
 // part [ceil(n / 256)] scratch; loss [1] and grad [n] out.
 hipError_t launch_l2(const float* v, const float* t, int64_t n, float* grad, float* part, float* loss,
                      hipStream_t st);
+hipError_t launch_soa(const float* a, const float* b, int64_t P, float* oa, float* ob, hipStream_t st);
 hipError_t launch_sgd(float* x, const float* g, int64_t n, float lr, hipStream_t st);
 
 }  // namespace shv

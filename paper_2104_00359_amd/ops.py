@@ -9,11 +9,23 @@ computation runs in the library's kernels.
 """
 from __future__ import annotations
 
+import ctypes
 import threading
 
 import torch
 
 from . import _lib
+try:
+    from . import _host
+except ImportError as e:
+    raise ImportError("paper_2104_00359_amd/_host.so is not built or does not load; run "
+                      "`python -c 'import __graft_entry__ as g; g.build()'`") from e
+
+# The entry points that the host side calls, in the order of its table.
+_host.bind(*(ctypes.cast(_lib.raw(f), ctypes.c_void_p).value for f in (
+    "shv_last_error", "shv_status_string", "shv_render_saved_floats", "sh_render_forward", "sh_render_backward",
+    "shv_saved_floats", "sh_visibility_forward", "sh_visibility_backward", "sh_shade_channels",
+    "sh_shade_channels_backward", "shv_internal_soa")))
 
 _ws_lock = threading.Lock()
 _ws_cache: dict = {}
@@ -33,12 +45,12 @@ def workspace(device: torch.device, nbytes: int) -> torch.Tensor:
     streams get different buffers.  The buffer is allocated on the stream
     that uses it, so when it grows the caching allocator reuses the old block
     only after the work already queued on that stream."""
-    stream = torch.cuda.current_stream(device)
-    key = (device.type, device.index, stream.cuda_stream)
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    key = (device.type, device.index, torch._C._cuda_getCurrentRawStream(index))
     with _ws_lock:
         buf = _ws_cache.get(key)
         if buf is None or buf.numel() < nbytes:
-            with torch.cuda.stream(stream):
+            with torch.cuda.stream(torch.cuda.current_stream(device)):
                 buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
             _ws_cache[key] = buf
         return buf
@@ -73,7 +85,9 @@ def check_inputs(op: str, specs) -> None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current device's current stream (its device's memory is in use, so
+    the runtime is up)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _soa(x: torch.Tensor) -> torch.Tensor:
@@ -91,45 +105,30 @@ class ShadeSH(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, points, normals, albedo, spheres, light, n_bands, eps, n_squarings):
-        P = points.shape[0] if isinstance(points, torch.Tensor) and points.dim() == 2 else None
-        S = spheres.shape[0] if isinstance(spheres, torch.Tensor) and spheres.dim() == 2 else None
         N = int(n_bands) * int(n_bands)
-        check_inputs("shade_sh", [("points", points, (P, 3)), ("normals", normals, (P, 3)),
-                                  ("albedo", albedo, (P,)), ("spheres", spheres, (S, 4)), ("light", light, (N,))])
+        if not (isinstance(light, torch.Tensor) and light.dim() == 1
+                and _host.inputs_ok(points, normals, albedo, spheres, light, N)):
+            P = points.shape[0] if isinstance(points, torch.Tensor) and points.dim() == 2 else None
+            S = spheres.shape[0] if isinstance(spheres, torch.Tensor) and spheres.dim() == 2 else None
+            check_inputs("shade_sh", [("points", points, (P, 3)), ("normals", normals, (P, 3)),
+                                      ("albedo", albedo, (P,)), ("spheres", spheres, (S, 4)), ("light", light, (N,))])
         dev = points.device
         ensure_init(dev)
         prm = _lib.params(n_bands, eps, n_squarings)
-        pts, nrm = _soa(points), _soa(normals)
-        alb, sph, L = _f32(albedo), _f32(spheres), _f32(light)
-        vis = torch.empty(N, P, dtype=torch.float32, device=dev)
-        saved = torch.empty(max(_lib.shv_render_saved_floats(P, prm), 1), dtype=torch.float32, device=dev)
-        rad = torch.empty(P, dtype=torch.float32, device=dev)
-        ws = workspace(dev, _lib.shv_workspace_bytes(P, S, prm))
-        _lib.sh_render_forward(pts, nrm, alb, sph, L, P, S, prm, vis, rad, saved, _lib.nbytes(saved), ws, ws.numel(),
-                               _stream())
-        ctx.save_for_backward(pts, nrm, alb, sph, vis, saved)
+        ws = workspace(dev, _lib.shv_workspace_bytes(points.shape[0], spheres.shape[0], prm))
+        rad, *keep = _host.shade_forward(points, normals, albedo, spheres, light, ctypes.addressof(prm), ws, _stream())
+        ctx.save_for_backward(*keep)
         ctx.cfg = (n_bands, eps, n_squarings)
         return rad
 
     @staticmethod
     def backward(ctx, grad_rad):
         pts, nrm, alb, sph, vis, saved = ctx.saved_tensors
-        n_bands, eps, n_squarings = ctx.cfg
-        prm = _lib.params(n_bands, eps, n_squarings)
-        dev = pts.device
-        P, S, N = pts.shape[1], sph.shape[0], n_bands * n_bands
-        gB = _f32(grad_rad)
-        need_p, need_n, need_a, need_s, need_l = ctx.needs_input_grad[:5]
-        gP = torch.empty(3, P, dtype=torch.float32, device=dev) if need_p else None
-        gN = torch.empty(3, P, dtype=torch.float32, device=dev) if need_n else None
-        gA = torch.empty(P, dtype=torch.float32, device=dev) if need_a else None
-        gS = torch.empty(S, 4, dtype=torch.float32, device=dev) if need_s else None
-        gL = torch.empty(N, dtype=torch.float32, device=dev) if need_l else None
-        ws = workspace(dev, _lib.shv_workspace_bytes(P, S, prm))
-        _lib.sh_render_backward(gB, pts, nrm, alb, sph, P, S, prm, vis, saved, _lib.nbytes(saved), gP, gN, gA, gS, gL,
-                                ws, ws.numel(), _stream())
-        return (gP.t() if gP is not None else None, gN.t() if gN is not None else None, gA, gS, gL,
-                None, None, None)
+        prm = _lib.params(*ctx.cfg)
+        ws = workspace(pts.device, _lib.shv_workspace_bytes(pts.shape[1], sph.shape[0], prm))
+        grads = _host.shade_backward(grad_rad, pts, nrm, alb, sph, vis, saved, ctypes.addressof(prm), ws, _stream(),
+                                     *ctx.needs_input_grad[:5])
+        return (*grads, None, None, None)
 
 
 def shade_sh(points, normals, albedo, spheres, light, n_bands: int, eps: float = 3.0, n_squarings: int = 4):
@@ -210,51 +209,37 @@ class ShadeSHChannels(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, points, normals, albedo, spheres, light, n_bands, eps, n_squarings, flags=0):
-        P = points.shape[0] if isinstance(points, torch.Tensor) and points.dim() == 2 else None
-        S = spheres.shape[0] if isinstance(spheres, torch.Tensor) and spheres.dim() == 2 else None
-        C = light.shape[0] if isinstance(light, torch.Tensor) and light.dim() == 2 else None
         N = int(n_bands) * int(n_bands)
-        check_inputs("shade_sh_channels", [("points", points, (P, 3)), ("normals", normals, (P, 3)),
-                                           ("albedo", albedo, (P, C)), ("spheres", spheres, (S, 4)),
-                                           ("light", light, (C, N))])
+        if not (isinstance(light, torch.Tensor) and light.dim() == 2
+                and _host.inputs_ok(points, normals, albedo, spheres, light, N)):
+            P = points.shape[0] if isinstance(points, torch.Tensor) and points.dim() == 2 else None
+            S = spheres.shape[0] if isinstance(spheres, torch.Tensor) and spheres.dim() == 2 else None
+            C = light.shape[0] if isinstance(light, torch.Tensor) and light.dim() == 2 else None
+            check_inputs("shade_sh_channels", [("points", points, (P, 3)), ("normals", normals, (P, 3)),
+                                               ("albedo", albedo, (P, C)), ("spheres", spheres, (S, 4)),
+                                               ("light", light, (C, N))])
         dev = points.device
         ensure_init(dev)
         prm = _lib.params(n_bands, eps, n_squarings, flags)
-        pts, nrm = _soa(points), _soa(normals)
-        alb, sph, L = _soa(albedo), _f32(spheres), _f32(light)
-        vis = torch.empty(N, P, dtype=torch.float32, device=dev)
-        saved = torch.empty(max(_lib.shv_saved_floats(P, prm), 1), dtype=torch.float32, device=dev)
-        rad = torch.empty(C, P, dtype=torch.float32, device=dev)
-        ws = workspace(dev, max(_lib.shv_workspace_bytes(P, S, prm), _lib.shv_channels_workspace_bytes(P, C, prm)))
-        _lib.sh_visibility_forward(pts, P, sph, S, prm, vis, saved, _lib.nbytes(saved), ws, ws.numel(), _stream())
-        _lib.sh_shade_channels(vis, nrm, alb, L, C, P, prm, rad, ws, ws.numel(), _stream())
-        ctx.save_for_backward(pts, nrm, alb, sph, L, vis, saved)
+        ws = workspace(dev, ShadeSHChannels._workspace_bytes(points.shape[0], spheres.shape[0], light.shape[0], prm))
+        rad, *keep = _host.channels_forward(points, normals, albedo, spheres, light, ctypes.addressof(prm), ws,
+                                            _stream())
+        ctx.save_for_backward(*keep)
         ctx.cfg = (n_bands, eps, n_squarings, flags)
-        return rad.t()
+        return rad
+
+    @staticmethod
+    def _workspace_bytes(P, S, C, prm):
+        return max(_lib.shv_workspace_bytes(P, S, prm), _lib.shv_channels_workspace_bytes(P, C, prm))
 
     @staticmethod
     def backward(ctx, grad_rad):
         pts, nrm, alb, sph, L, vis, saved = ctx.saved_tensors
-        n_bands, eps, n_squarings, flags = ctx.cfg
-        prm = _lib.params(n_bands, eps, n_squarings, flags)
-        dev = pts.device
-        P, S, N, C = pts.shape[1], sph.shape[0], n_bands * n_bands, L.shape[0]
-        gB = _soa(grad_rad)
-        need_p, need_n, need_a, need_s, need_l = ctx.needs_input_grad[:5]
-        need_v = need_p or need_s
-        gV = torch.empty(N, P, dtype=torch.float32, device=dev) if need_v else None
-        gN = torch.empty(3, P, dtype=torch.float32, device=dev) if need_n else None
-        gA = torch.empty(C, P, dtype=torch.float32, device=dev) if need_a else None
-        gL = torch.empty(C, N, dtype=torch.float32, device=dev) if need_l else None
-        gP = torch.empty(3, P, dtype=torch.float32, device=dev) if need_p else None
-        gS = torch.empty(S, 4, dtype=torch.float32, device=dev) if need_s else None
-        ws = workspace(dev, max(_lib.shv_workspace_bytes(P, S, prm), _lib.shv_channels_workspace_bytes(P, C, prm)))
-        _lib.sh_shade_channels_backward(gB, vis, nrm, alb, L, C, P, prm, gV, gN, gA, gL, ws, ws.numel(), _stream())
-        if need_v:
-            _lib.sh_visibility_backward(gV, vis, pts, P, sph, S, prm, saved, _lib.nbytes(saved), gP, gS, ws, ws.numel(),
-                                        _stream())
-        return (gP.t() if gP is not None else None, gN.t() if gN is not None else None,
-                gA.t() if gA is not None else None, gS, gL, None, None, None, None)
+        prm = _lib.params(*ctx.cfg)
+        ws = workspace(pts.device, ShadeSHChannels._workspace_bytes(pts.shape[1], sph.shape[0], L.shape[0], prm))
+        grads = _host.channels_backward(grad_rad, pts, nrm, alb, sph, L, vis, saved, ctypes.addressof(prm), ws,
+                                        _stream(), *ctx.needs_input_grad[:5])
+        return (*grads, None, None, None, None)
 
 
 def shade_sh_channels(points, normals, albedo, spheres, light, n_bands: int, eps: float = 3.0,
