@@ -223,9 +223,11 @@ bool exp_four_waves(int nb, int64_t P, uint32_t flags, bool batched) {
   // One receiver per lane needs no exchange through LDS and no barriers, but a
   // launch then has 4x fewer blocks and a wave has 4x the work, so a single
   // scene takes it only once it fills the chip.  Up to 6 bands that is from 256
-  // blocks (65,536 receivers) up.  At 7 and 8 bands forward + adjoint take
-  // 128 us against 109 in four waves at 65,536 receivers (8 bands, k = 4), 143
-  // against 154 at 98,304 and 344 against 440 at 262,144.  A batch's up to 6
+  // blocks (65,536 receivers) up (6 bands, k = 4: forward + adjoint 58 us against
+  // 57 in four waves there, 69 against 71 at 81,920, 76 against 102 at 131,072;
+  // 54 against 47 at 40,000).  At 7 and 8 bands it is 128 us against 111 at
+  // 65,536 (8 bands), 142 against 149 at 98,304 and 343 against 407 at 262,144.
+  // A batch's up to 6
   // bands always take it; above, a batch counts as four waves per 64 receivers
   // and its kernels apply the size rule to the whole launch (batch_wide).
   return !(nb <= 6 ? batched || P >= 65536 : !batched && P >= SHV_EXP_WIDE_RECEIVERS);

@@ -438,8 +438,24 @@ __global__ __launch_bounds__(SHV_BLOCK, 2) void k_exp_bwd(const float* __restric
 // ===========================================================================
 // Four waves per 64 receivers; wave G owns output group G.
 
+// LDS of the four-wave forward.  Where products go through latitudes, the
+// coefficients are exchanged once before and once after the squarings, and the
+// squarings' exchange overlays that buffer.
+template <int NB>
+struct Fwd4Loop {
+  LatShared<NB, true, 1> lat;
+};
+template <int NB>
+union Exp4FwdShared {
+  struct {
+    float X[Lat<NB>::USE ? 1 : 2][NB * NB][64];
+  } s;
+  std::conditional_t<Lat<NB>::USE, Fwd4Loop<NB>, int> loop;
+  float Ms[MSupp<NB>::SIZE];
+};
+
 template <int NB, int G, bool SHADE>
-__device__ __forceinline__ void exp_fwd_group(float (*X)[NB * NB][64], float (*Bx)[64], int lane, int64_t p, bool ok,
+__device__ __forceinline__ void exp_fwd_group(Exp4FwdShared<NB>& sh, float (*Bx)[64], int lane, int64_t p, bool ok,
                                               const float* __restrict__ Fpart, int nchunks, int64_t P, float eps,
                                               int k, float* __restrict__ vis, float* __restrict__ saved,
                                               const ShadeArgs& sa) {
@@ -457,6 +473,7 @@ __device__ __forceinline__ void exp_fwd_group(float (*X)[NB * NB][64], float (*B
     for (int i = 0; i < N; ++i)
       if (fgroup_of<NB>(i) == G) F[i] += sel0(ok, src[(int64_t)i * P]);
   }
+  auto& X = sh.s.X;
 #pragma unroll
   for (int i = 0; i < N; ++i)
     if (fgroup_of<NB>(i) == G) X[0][i][lane] = F[i];
@@ -466,6 +483,7 @@ __device__ __forceinline__ void exp_fwd_group(float (*X)[NB * NB][64], float (*B
   for (int i = 0; i < N; ++i) E[i] = X[0][i][lane];
   const float c = exp_prologue<NB>(E, eps, k);
   if (G == 0 && saved && ok) saved[p] = c;
+  if constexpr (Lat<NB>::USE) __syncthreads();  // the squarings' buffer overlays X
   for (int j = 0; j < k; ++j) {
     if (saved && ok) {
       float* dst = saved + (int64_t)(1 + j * N) * P + p;
@@ -473,14 +491,29 @@ __device__ __forceinline__ void exp_fwd_group(float (*X)[NB * NB][64], float (*B
       for (int i = 0; i < N; ++i)
         if (fgroup_of<NB>(i) == G) dst[(int64_t)i * P] = E[i];
     }
-    SqGroup<NB, G>::square(E, O);
-    const int b = (j + 1) & 1;
+    if constexpr (Lat<NB>::USE) {
+      lat_product4<NB, G, true, 1>(E, E, O, sh.loop.lat, lane);
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (fgroup_of<NB>(i) == G) E[i] = O[i];
+    } else {
+      SqGroup<NB, G>::square(E, O);
+      const int b = (j + 1) & 1;
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (fgroup_of<NB>(i) == G) X[b][i][lane] = O[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < N; ++i) E[i] = X[b][i][lane];
+    }
+  }
+  if constexpr (Lat<NB>::USE) {  // the last square, complete in every wave
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      if (fgroup_of<NB>(i) == G) X[b][i][lane] = O[i];
+      if (fgroup_of<NB>(i) == G) X[0][i][lane] = E[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < N; ++i) E[i] = X[b][i][lane];
+    for (int i = 0; i < N; ++i) E[i] = X[0][i][lane];
   }
   const float ec = expf(c);
 #pragma unroll
@@ -491,9 +524,10 @@ __device__ __forceinline__ void exp_fwd_group(float (*X)[NB * NB][64], float (*B
       if (fgroup_of<NB>(i) == G) vis[(int64_t)i * P + p] = E[i];
   }
   if constexpr (SHADE) {
-    // After the last barrier above every wave has read its final squares:
-    // the other exchange buffer is free for the staged M.
-    float* Ms = &X[(k + 1) & 1][0][0];
+    // The exchange buffer that no wave reads any more is free for the staged M:
+    // the other one of two, or the only one once all have read it.
+    if constexpr (Lat<NB>::USE) __syncthreads();
+    float* Ms = Lat<NB>::USE ? sh.Ms : &X[Lat<NB>::USE ? 0 : (k + 1) & 1][0][0];
     stage_M<NB>(sa.M, Ms, G * 64 + lane);
     float H[N], Hb[N], nx, ny, nz, ux, uy, uz;
     load_normal(sa.nrm, P, p, ok, nx, ny, nz);
@@ -506,23 +540,23 @@ __device__ __forceinline__ void exp_fwd_group(float (*X)[NB * NB][64], float (*B
 }
 
 template <int NB>
-struct Exp4FwdShared {
-  float X[2][NB * NB][64];
-  float Bx[4][64];
+struct Exp4FwdBlock {
+  Exp4FwdShared<NB> x;
+  float Bx[4][64];  // shading partial per support-column group
 };
 
 template <int NB, bool SHADE>
 __device__ __forceinline__ void exp_fwd4_item(const float* __restrict__ Fpart, int nchunks, int64_t P, float eps,
                                               int k, float* __restrict__ vis, float* __restrict__ saved,
-                                              const ShadeArgs& sa, int64_t bx, Exp4FwdShared<NB>& sh) {
+                                              const ShadeArgs& sa, int64_t bx, Exp4FwdBlock<NB>& sh) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t p = bx * 64 + lane;
   const bool ok = p < P;
   switch (wave) {
-    case 0: exp_fwd_group<NB, 0, SHADE>(sh.X, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
-    case 1: exp_fwd_group<NB, 1, SHADE>(sh.X, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
-    case 2: exp_fwd_group<NB, 2, SHADE>(sh.X, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
-    default: exp_fwd_group<NB, 3, SHADE>(sh.X, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
+    case 0: exp_fwd_group<NB, 0, SHADE>(sh.x, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
+    case 1: exp_fwd_group<NB, 1, SHADE>(sh.x, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
+    case 2: exp_fwd_group<NB, 2, SHADE>(sh.x, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
+    default: exp_fwd_group<NB, 3, SHADE>(sh.x, sh.Bx, lane, p, ok, Fpart, nchunks, P, eps, k, vis, saved, sa); break;
   }
 }
 
@@ -530,7 +564,7 @@ template <int NB, bool SHADE>
 __global__ __launch_bounds__(SHV_BLOCK) void k_exp_fwd4(const float* __restrict__ Fpart, int nchunks, int64_t P,
                                                         float eps, int k, float* __restrict__ vis,
                                                         float* __restrict__ saved, ShadeArgs sa) {
-  __shared__ Exp4FwdShared<NB> sh;
+  __shared__ Exp4FwdBlock<NB> sh;
   exp_fwd4_item<NB, SHADE>(Fpart, nchunks, P, eps, k, vis, saved, sa, blockIdx.x, sh);
 }
 
@@ -551,9 +585,22 @@ struct Bwd4Loop {
   float T[2][NB * NB][64];
 };
 
+// Where products go through latitudes each wave keeps its own orders of E_j and
+// of the cotangent in registers; the waves exchange Fourier coefficients, in two
+// phases at 7 and 8 bands, so that two blocks share a CU, and once at the end
+// E_0 and its cotangent.
+template <int NB>
+union Bwd4LatLoop {
+  static constexpr int PH = NB >= 7 ? 2 : 1;
+  LatShared<NB, false, PH> lat;
+  float X[2][NB * NB][64];
+};
+template <int NB>
+using Bwd4LoopOf = std::conditional_t<Lat<NB>::USE, Bwd4LatLoop<NB>, Bwd4Loop<NB>>;
+
 template <int NB, int G, bool SHADE>
 __device__ __forceinline__ void exp_bwd_group(float (*X)[NB * NB][64], Bwd4Shared& sh, LightTile& LT, float* Ms,
-                                              Bwd4Loop<NB>& LB, int64_t bx,
+                                              Bwd4LoopOf<NB>& LB, int64_t bx,
                                               int lane, int64_t p, bool ok, const float* __restrict__ gIn,
                                               const float* __restrict__ vis, const float* __restrict__ saved,
                                               int64_t P, float eps, int k, float* __restrict__ Wout,
@@ -655,43 +702,73 @@ __device__ __forceinline__ void exp_bwd_group(float (*X)[NB * NB][64], Bwd4Share
       if (group_of<NB>(i) == G) pre[i] = sel0(ok, src[(int64_t)i * P]);
   }
   __syncthreads();  // every wave has read X and the partials: the loop buffers overlay them from here
-  if (k > 0) {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      if (group_of<NB>(i) == G) LB.E[(k - 1) & 1][i][lane] = pre[i];
-    if (k > 1) {
-      const float* src = saved + (int64_t)(1 + (k - 2) * N) * P + q;
+  if constexpr (Lat<NB>::USE) {
+    for (int j = k - 1; j >= 0; --j) {
 #pragma unroll
       for (int i = 0; i < N; ++i)
-        if (group_of<NB>(i) == G) pre[i] = sel0(ok, src[(int64_t)i * P]);
-    }
-    __syncthreads();
-  }
-  // Step j reads E_j from LB.E[j & 1] (complete since the previous barrier),
-  // stores its group of E_{j-1} into the other buffer (last read at step
-  // j + 1, before that barrier), and exchanges its outputs through
-  // LB.T[j & 1] (last read at step j + 2): one barrier per step.
-  for (int j = k - 1; j >= 0; --j) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) E[i] = LB.E[j & 1][i][lane];
-    if (j > 0) {
-#pragma unroll
-      for (int i = 0; i < N; ++i)
-        if (group_of<NB>(i) == G) LB.E[(j - 1) & 1][i][lane] = pre[i];
-      if (j > 1) {
-        const float* src = saved + (int64_t)(1 + (j - 2) * N) * P + q;
+        if (group_of<NB>(i) == G) E[i] = pre[i];
+      if (j > 0) {
+        const float* src = saved + (int64_t)(1 + (j - 1) * N) * P + q;
 #pragma unroll
         for (int i = 0; i < N; ++i)
           if (group_of<NB>(i) == G) pre[i] = sel0(ok, src[(int64_t)i * P]);
       }
-    }
-    SqGroup<NB, G>::adj(Eb, E, T);
+      lat_product4<NB, G, false, Bwd4LatLoop<NB>::PH>(E, Eb, T, LB.lat, lane);
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-      if (group_of<NB>(i) == G) LB.T[j & 1][i][lane] = T[i];
+      for (int i = 0; i < N; ++i)
+        if (group_of<NB>(i) == G) Eb[i] = T[i];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (group_of<NB>(i) != G) continue;
+      LB.X[0][i][lane] = E[i];
+      LB.X[1][i][lane] = Eb[i];
+    }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < N; ++i) Eb[i] = LB.T[j & 1][i][lane];
+    for (int i = 0; i < N; ++i) {
+      E[i] = LB.X[0][i][lane];
+      Eb[i] = LB.X[1][i][lane];
+    }
+  } else {
+    if (k > 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (group_of<NB>(i) == G) LB.E[(k - 1) & 1][i][lane] = pre[i];
+      if (k > 1) {
+        const float* src = saved + (int64_t)(1 + (k - 2) * N) * P + q;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          if (group_of<NB>(i) == G) pre[i] = sel0(ok, src[(int64_t)i * P]);
+      }
+      __syncthreads();
+    }
+    // Step j reads E_j from LB.E[j & 1] (complete since the previous barrier),
+    // stores its group of E_{j-1} into the other buffer (last read at step
+    // j + 1, before that barrier), and exchanges its outputs through
+    // LB.T[j & 1] (last read at step j + 2): one barrier per step.
+    for (int j = k - 1; j >= 0; --j) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) E[i] = LB.E[j & 1][i][lane];
+      if (j > 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          if (group_of<NB>(i) == G) LB.E[(j - 1) & 1][i][lane] = pre[i];
+        if (j > 1) {
+          const float* src = saved + (int64_t)(1 + (j - 2) * N) * P + q;
+#pragma unroll
+          for (int i = 0; i < N; ++i)
+            if (group_of<NB>(i) == G) pre[i] = sel0(ok, src[(int64_t)i * P]);
+        }
+      }
+      SqGroup<NB, G>::adj(Eb, E, T);
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (group_of<NB>(i) == G) LB.T[j & 1][i][lane] = T[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < N; ++i) Eb[i] = LB.T[j & 1][i][lane];
+    }
   }
   if (!ok) return;
   exp_epilogue<NB>(E, Eb, cbar, eps, k, P, p, Wout, [](int i) { return group_of<NB>(i) == G; });
@@ -708,7 +785,7 @@ struct Exp4BwdSetup {
 template <int NB>
 union Exp4BwdShared {
   Exp4BwdSetup<NB> s;  // the shading adjoint and the set-up of the squarings
-  Bwd4Loop<NB> loop;   // the adjoint squarings (overlays s: a barrier separates them)
+  Bwd4LoopOf<NB> loop;  // the adjoint squarings (overlays s: a barrier separates them)
 };
 
 template <int NB, bool SHADE>
@@ -784,7 +861,7 @@ __device__ __forceinline__ bool batch_wide(const BatchView& v, const BatchScene&
 template <int NB, bool FOUR>
 __global__ __launch_bounds__(SHV_BLOCK, FOUR && NB < 7 ? 1 : Fwd1Waves<NB>::VALUE) void k_batch_exp_fwd(
     const char* __restrict__ table) {
-  __shared__ Exp4FwdShared<NB> sh;
+  __shared__ Exp4FwdBlock<NB> sh;
   const BatchView v(table);
   const int64_t item = blockIdx.x;
   if (item >= v.h->total_exp[FOUR][NB]) return;
@@ -796,13 +873,13 @@ __global__ __launch_bounds__(SHV_BLOCK, FOUR && NB < 7 ? 1 : Fwd1Waves<NB>::VALU
       if (batch_wide<NB>(v, S)) {  // uniform
         if (4 * (item - S.off_exp) >= S.n_exp) return;
         exp_fwd1_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa,
-                                S.exp_block0 / 4 + (item - S.off_exp), &sh.X[0][0][0]);
+                                S.exp_block0 / 4 + (item - S.off_exp), sh.x.Ms);
         return;
       }
     }
     exp_fwd4_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa, bx, sh);
   } else {
-    exp_fwd1_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa, bx, &sh.X[0][0][0]);
+    exp_fwd1_item<NB, true>(S.Fpart, S.nchunks_f, S.P, S.eps, S.k, S.vis, S.saved, sa, bx, sh.x.Ms);
   }
 }
 

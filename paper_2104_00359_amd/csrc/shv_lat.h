@@ -99,29 +99,34 @@ __device__ __forceinline__ constexpr bool lat_has(int m) { return G < 0 || group
 template <int NB>
 __device__ __forceinline__ constexpr int lat_at(int m) { return m * NB - m * (m - 1) / 2; }
 
-// Fourier coefficients of the function with coefficients e(i) at z (index 0) and
-// -z (1), or at the equator (EQ; the odd terms vanish); without its mean unless
-// MEAN.
+// Order m of the Fourier coefficients of the function with coefficients e(i), at
+// z (index 0) and -z (1), or at the equator (EQ; the odd terms vanish); without
+// its mean unless MEAN.
+template <int NB, bool EQ, bool MEAN, class Coef>
+__device__ __forceinline__ void lat_up_order(Coef e, const float* __restrict__ Q, int m, float (&A)[2][NB],
+                                             float (&B)[2][NB]) {
+#pragma clang fp contract(off)  // the sums of two products below round alike in every kernel
+  float a[2] = {0.0f, 0.0f}, b[2] = {0.0f, 0.0f};
+  bool on[2] = {false, false};
+#pragma unroll
+  for (int l = m; l < NB; ++l) {
+    const int s = (l - m) & 1;
+    if ((l == 0 && !MEAN) || (EQ && s)) continue;
+    const float t = Q[lat_at<NB>(m) + l - m];
+    a[s] = on[s] ? fmaf(t, e(idx(l, m)), a[s]) : t * e(idx(l, m));
+    if (m > 0) b[s] = on[s] ? fmaf(t, e(idx(l, -m)), b[s]) : t * e(idx(l, -m));
+    on[s] = true;
+  }
+  A[0][m] = EQ ? a[0] : a[0] + a[1];
+  A[1][m] = EQ ? 0.0f : a[0] - a[1];
+  B[0][m] = EQ ? b[0] : b[0] + b[1];
+  B[1][m] = EQ ? 0.0f : b[0] - b[1];
+}
+
 template <int NB, bool EQ, bool MEAN, class Coef>
 __device__ __forceinline__ void lat_up(Coef e, const float* __restrict__ Q, float (&A)[2][NB], float (&B)[2][NB]) {
 #pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    float a[2] = {0.0f, 0.0f}, b[2] = {0.0f, 0.0f};
-    bool on[2] = {false, false};
-#pragma unroll
-    for (int l = m; l < NB; ++l) {
-      const int s = (l - m) & 1;
-      if ((l == 0 && !MEAN) || (EQ && s)) continue;
-      const float t = Q[lat_at<NB>(m) + l - m];
-      a[s] = on[s] ? fmaf(t, e(idx(l, m)), a[s]) : t * e(idx(l, m));
-      if (m > 0) b[s] = on[s] ? fmaf(t, e(idx(l, -m)), b[s]) : t * e(idx(l, -m));
-      on[s] = true;
-    }
-    A[0][m] = EQ ? a[0] : a[0] + a[1];
-    A[1][m] = EQ ? 0.0f : a[0] - a[1];
-    B[0][m] = EQ ? b[0] : b[0] + b[1];
-    B[1][m] = EQ ? 0.0f : b[0] - b[1];
-  }
+  for (int m = 0; m < NB; ++m) lat_up_order<NB, EQ, MEAN>(e, Q, m, A, B);
 }
 
 // Order m of half the square of c = A - i B (the weight's factor 2 makes it whole).
@@ -182,15 +187,13 @@ __device__ __forceinline__ void lat_mul(const float (&A)[NB], const float (&B)[N
   }
 }
 
-// One row of a product: o += its share (o = its share for the first row), for
-// the orders of group G.  SQUARE:
-// (e - mean)^2, else twice (e - mean) h.
-template <int NB, int G, bool SQUARE, bool EQ, class Coef>
-__device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const float* __restrict__ Q, bool first,
-                                        float (&o)[NB * NB]) {
-  float A[2][NB], B[2][NB], X[2][NB], Y[2][NB];
-  lat_up<NB, EQ, false>(e, Q, A, B);
-  if constexpr (!SQUARE) lat_up<NB, EQ, true>([&](int i) { return h[i]; }, Q, X, Y);
+// One row of a product from the factors' Fourier coefficients: o += its share
+// (o = its share for the first row), for the orders of group G.  SQUARE: (e -
+// mean)^2, else twice (e - mean) h.
+template <int NB, int G, bool SQUARE, bool EQ>
+__device__ __forceinline__ void lat_down(const float (&A)[2][NB], const float (&B)[2][NB], const float (&X)[2][NB],
+                                         const float (&Y)[2][NB], const float* __restrict__ Q, bool first,
+                                         float (&o)[NB * NB]) {
 #pragma unroll
   for (int m = 0; m < NB; ++m) {
     if (!lat_has<NB, G>(m)) continue;
@@ -212,6 +215,15 @@ __device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const
       if (m > 0) o[idx(l, -m)] = first ? t * vb : fmaf(t, vb, o[idx(l, -m)]);
     }
   }
+}
+
+template <int NB, int G, bool SQUARE, bool EQ, class Coef>
+__device__ __forceinline__ void lat_row(Coef e, const float (&h)[NB * NB], const float* __restrict__ Q, bool first,
+                                        float (&o)[NB * NB]) {
+  float A[2][NB], B[2][NB], X[2][NB], Y[2][NB];
+  lat_up<NB, EQ, false>(e, Q, A, B);
+  if constexpr (!SQUARE) lat_up<NB, EQ, true>([&](int i) { return h[i]; }, Q, X, Y);
+  lat_down<NB, G, SQUARE, EQ>(A, B, X, Y, Q, first, o);
 }
 
 // The outputs of group G (-1: all): o = e * e (SQUARE) or o = 2 (h * e), e(i)
@@ -242,6 +254,91 @@ template <int NB, int G, bool SQUARE>
 __device__ __forceinline__ void lat_product(const float (&e)[NB * NB], const float (&h)[NB * NB],
                                             float (&o)[NB * NB]) {
   lat_product<NB, G, SQUARE>([&](int i) { return e[i]; }, h, o, [] {});
+}
+
+// The same product by the four waves of a block, wave G holding the
+// coefficients of its own orders only, of the factors and of the outputs: it
+// transforms its orders up, the waves exchange Fourier coefficients through LDS
+// (lane by lane, 16 bytes per order, row and factor), and each forms its own
+// outputs from all of them.  Against exchanging coefficients and transforming
+// all of them in every wave, the transforms up, half of a wave's work in the
+// adjoint and a third in the squaring, are done once.  PH: phases of rows, which
+// bound the buffer.  The bits are those of lat_product.  Ends with a barrier.
+// Bound: up to a few blocks per CU by what one wave issues (an instruction in
+// four cycles at best) and by the barriers; forward and adjoint of the
+// exponential, k = 4, us before and after: 6 bands 20.0 + 38.8 -> 18.3 + 36.2 at
+// 50,000 receivers, 8 bands 40.0 + 77.4 -> 37.5 + 74.4 at 65,000, 20.9 + 36.1 ->
+// 21.1 + 36.5 at 20,000.
+template <int NB, bool SQUARE, int PH>
+struct LatShared {
+  static constexpr int ROWS = (LatTab<NB>::PAIRS + LatTab<NB>::EQ + PH - 1) / PH, F = SQUARE ? 1 : 2;
+  float4 q[ROWS * F * NB][64];
+  float mean[64];
+};
+
+template <int NB, int G, bool SQUARE, int PH>
+__device__ __forceinline__ void lat_product4(const float (&e)[NB * NB], const float (&h)[NB * NB], float (&o)[NB * NB],
+                                             LatShared<NB, SQUARE, PH>& sh, int lane) {
+  constexpr int N = NB * NB, QP = Lat<NB>::QP, PAIRS = LatTab<NB>::PAIRS, ROWS = PAIRS + LatTab<NB>::EQ;
+  constexpr int PER = LatShared<NB, SQUARE, PH>::ROWS, F = LatShared<NB, SQUARE, PH>::F;
+  const float* __restrict__ Q = LatTab<NB>::rows();
+  const auto ce = [&](int i) { return e[i]; };
+  const auto ch = [&](int i) { return h[i]; };
+  if (lat_has<NB, G>(0)) sh.mean[lane] = e[0];
+  float t0 = 0.0f;
+#pragma unroll
+  for (int ph = 0; ph < PH; ++ph) {
+    float A[PER][2][NB], B[PER][2][NB], X[PER][2][NB], Y[PER][2][NB];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int t = ph * PER + u;
+      if (t >= ROWS) continue;
+#pragma unroll
+      for (int m = 0; m < NB; ++m) {
+        if (!lat_has<NB, G>(m)) continue;
+        if (t < PAIRS) lat_up_order<NB, false, false>(ce, Q + t * QP, m, A[u], B[u]);
+        else lat_up_order<NB, true, false>(ce, Q + t * QP, m, A[u], B[u]);
+        sh.q[(u * F) * NB + m][lane] = make_float4(A[u][0][m], A[u][1][m], B[u][0][m], B[u][1][m]);
+        if constexpr (!SQUARE) {
+          if (t < PAIRS) lat_up_order<NB, false, true>(ch, Q + t * QP, m, X[u], Y[u]);
+          else lat_up_order<NB, true, true>(ch, Q + t * QP, m, X[u], Y[u]);
+          sh.q[(u * F + 1) * NB + m][lane] = make_float4(X[u][0][m], X[u][1][m], Y[u][0][m], Y[u][1][m]);
+        }
+      }
+    }
+    __syncthreads();
+    if (ph == 0) t0 = 2.0f * sh.mean[lane];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int t = ph * PER + u;
+      if (t >= ROWS) continue;
+#pragma unroll
+      for (int m = 0; m < NB; ++m) {
+        if (lat_has<NB, G>(m)) continue;
+        const float4 v = sh.q[(u * F) * NB + m][lane];
+        A[u][0][m] = v.x;
+        A[u][1][m] = v.y;
+        B[u][0][m] = v.z;
+        B[u][1][m] = v.w;
+        if constexpr (!SQUARE) {
+          const float4 w = sh.q[(u * F + 1) * NB + m][lane];
+          X[u][0][m] = w.x;
+          X[u][1][m] = w.y;
+          Y[u][0][m] = w.z;
+          Y[u][1][m] = w.w;
+        }
+      }
+      if (t < PAIRS) lat_down<NB, G, SQUARE, false>(A[u], B[u], X[u], Y[u], Q + t * QP, t == 0, o);
+      else lat_down<NB, G, SQUARE, true>(A[u], B[u], X[u], Y[u], Q + t * QP, t == 0, o);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (group_of<NB>(i) != G) continue;
+    if constexpr (SQUARE) o[i] = i == 0 ? fmaf(e[0], e[0], o[0]) : fmaf(t0, e[i], o[i]);
+    else o[i] = fmaf(t0, h[i], o[i]);
+  }
 }
 
 }  // namespace shv

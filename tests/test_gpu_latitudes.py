@@ -91,3 +91,17 @@ def test_large_launches_keep_the_four_wave_bits(n):
     for got, ref in [(single, refs[0])] + [(collect(b), r) for b, r in zip(bufs, refs)]:
         for key in ("V", "B") + GRADS:
             assert np.array_equal(got[key], ref[key]), key
+
+
+@pytest.mark.parametrize("n", [6, 7, 8])
+@pytest.mark.parametrize("k", [0, 1, 2, 3])
+def test_four_waves_at_every_parity_of_the_squarings(n, k):
+    """The waves' exchange before, between and after k squarings."""
+    L = lib()
+    sc = scenegen.scene_random_shell(1100 + n, 65, 7, n)
+    sc["spheres"][:, 3] *= 0.5
+    four = run_render(sc, sc["grad_radiance"], k=k, flags=L.SHV_FLAG_EXP_FOUR_WAVES)
+    one = run_render(sc, sc["grad_radiance"], k=k, flags=L.SHV_FLAG_EXP_ONE_WAVE)
+    for key in ("V", "B") + GRADS:
+        assert np.array_equal(one[key], four[key]), key
+    assert all(np.isfinite(four[key]).all() for key in ("V", "B") + GRADS)
