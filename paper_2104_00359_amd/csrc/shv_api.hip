@@ -774,7 +774,7 @@ shv_status sh_envmap_project(const float* image, int channels, int64_t H, int64_
   SHV_TRY(launch("envmap_rows", stream,
                  [&] { return shv::launch_envmap_rows(nb, image, channels, H, W, part, stream); }));
   SHV_TRY(launch("reduce_envmap", stream, [&] {
-    return shv::launch_reduce_rows(part, (int)shv::envmap_row_blocks(H, W), N, light, stream, channels);
+    return shv::launch_reduce_rows(part, (int)shv::envmap_row_blocks(H), N, light, stream, channels);
   }));
   return SHV_OK;
 }

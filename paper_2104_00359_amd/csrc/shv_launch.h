@@ -42,15 +42,10 @@ hipError_t launch_shade_ch_bwd(int nb, const float* gB, const float* vis, const 
                                const float* M, int channels, int64_t P, float* gV, float* gN, float* gA,
                                float* Lpart, hipStream_t st);
 // Partial sums of Eq. 9 over an equirectangular map [channels][H][W], one per block of
-// envmap_row_blocks(H, W) row blocks -> part [channels][row blocks][N].
+// envmap_row_blocks(H) row blocks -> part [channels][row blocks][N].
 hipError_t launch_envmap_rows(int nb, const float* img, int channels, int64_t H, int64_t W, float* part,
                               hipStream_t st);
-int64_t envmap_row_blocks(int64_t H, int64_t W);
-// Rows per block of that projection: about 4096 pixels per block.
-inline int envmap_rows_per_block(int64_t W) {
-  const int64_t r = (4096 + W - 1) / W;
-  return (int)(r < 1 ? 1 : (r > SHV_ENV_MAX_ROWS ? SHV_ENV_MAX_ROWS : r));
-}
+int64_t envmap_row_blocks(int64_t H);
 hipError_t launch_exp_bwd(int nb, const float* gV, const float* vis, const float* saved, int64_t P,
                           float eps, int k, float* W, uint32_t flags, hipStream_t st);
 // The exponential by quadrature projection (SHV_FLAG_EXP_QUADRATURE); saved holds F [N][P].
