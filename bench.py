@@ -272,8 +272,7 @@ def roofline(kernels, steps, work):
         return None
     per_launch = flops_step * steps / kernels[dom]["launches"]
     ach = per_launch / (kernels[dom]["avg_us"] * 1e-6) / 1e12
-    bound = "mfma" if dom.startswith("exp_quad") else "alu"   # FP32 MFMA and FP32 vector share the peak
-    out = {"bound": bound, "kernel": dom, "achieved": round(ach, 3), "peak": PEAK_FP32_TFLOPS,
+    out = {"bound": "alu", "kernel": dom, "achieved": round(ach, 3), "peak": PEAK_FP32_TFLOPS,
            "unit": "TFLOP/s", "frac": round(ach / PEAK_FP32_TFLOPS, 4), "traffic": None,
            "flops_per_launch": int(per_launch), "avg_launch_us": kernels[dom]["avg_us"]}
     if unmodelled is not None:

@@ -300,7 +300,7 @@ __global__ __launch_bounds__(SHV_BLOCK, Fwd1Waves<NB>::VALUE) void k_exp_fwd(
 // At 7 and 8 bands the one-wave adjoint keeps E_j in LDS, one column per lane:
 // with it the cotangent, the outputs and one row's Fourier coefficients are all
 // the registers hold, 256 and two waves per SIMD instead of 390 and one (222 us
-// for 262,144 receivers at 8 bands, k = 4; four waves per receiver take 315).
+// for 262,144 receivers at 8 bands, k = 4; four waves per receiver take 288).
 // What bounds it is the FP32 issue of the rows: a wave issues one instruction
 // in about 5 cycles, and two waves share a SIMD.
 template <int NB>

@@ -263,7 +263,9 @@ __device__ __forceinline__ void lat_product(const float (&e)[NB * NB], const flo
 // outputs from all of them.  Against exchanging coefficients and transforming
 // all of them in every wave, the transforms up, half of a wave's work in the
 // adjoint and a third in the squaring, are done once.  PH: phases of rows, which
-// bound the buffer.  The bits are those of lat_product.  Ends with a barrier.
+// bound the buffer.  PIN: the sums are formed before each phase's last barrier;
+// where a branch follows, the compiler otherwise moves them behind it and holds
+// all that was read.  The bits are those of lat_product.  Ends with a barrier.
 // Bound: up to a few blocks per CU by what one wave issues (an instruction in
 // four cycles at best) and by the barriers; forward and adjoint of the
 // exponential, k = 4, us before and after: 6 bands 20.0 + 38.8 -> 18.3 + 36.2 at
@@ -276,7 +278,7 @@ struct LatShared {
   float mean[64];
 };
 
-template <int NB, int G, bool SQUARE, int PH>
+template <int NB, int G, bool SQUARE, int PH, bool PIN = false>
 __device__ __forceinline__ void lat_product4(const float (&e)[NB * NB], const float (&h)[NB * NB], float (&o)[NB * NB],
                                              LatShared<NB, SQUARE, PH>& sh, int lane) {
   constexpr int N = NB * NB, QP = Lat<NB>::QP, PAIRS = LatTab<NB>::PAIRS, ROWS = PAIRS + LatTab<NB>::EQ;
@@ -330,6 +332,11 @@ __device__ __forceinline__ void lat_product4(const float (&e)[NB * NB], const fl
       }
       if (t < PAIRS) lat_down<NB, G, SQUARE, false>(A[u], B[u], X[u], Y[u], Q + t * QP, t == 0, o);
       else lat_down<NB, G, SQUARE, true>(A[u], B[u], X[u], Y[u], Q + t * QP, t == 0, o);
+    }
+    if constexpr (PIN) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (group_of<NB>(i) == G) asm volatile("" : "+v"(o[i]));
     }
     __syncthreads();
   }

@@ -17,8 +17,11 @@
 // 1 + (k + 1 + j - 1) N + i = R_j[i] (1 <= j < K).
 //
 // Layout: four waves per 64 receivers, wave G owning one output group of each
-// product, the full vectors exchanged through double-buffered LDS (as the
-// four-wave squaring kernels).
+// product (as the four-wave squaring kernels).  Up to 5 bands the full vectors
+// are exchanged through double-buffered LDS; above, products go through
+// latitudes and a wave keeps its own orders of every vector in registers
+// (lat_product4), so only c and the cotangent's part of it cross LDS besides the
+// Fourier coefficients.
 
 #pragma once
 
@@ -32,6 +35,157 @@ struct TaylorShared {
   float Gx[NB * NB][64];  // G, read in full by every wave in the adjoint
   float Cb[4][64];        // cbar partial per output group
 };
+
+template <int NB>
+struct TaylorLatShared {
+  static constexpr int PH = NB >= 7 ? 2 : 1;
+  union {
+    LatShared<NB, true, 1> square;
+    LatShared<NB, false, PH> product;
+  };
+  float Cb[4][64];  // c, or the cbar partial per output group
+};
+template <int NB>
+using TaylorSharedOf = std::conditional_t<Lat<NB>::USE, TaylorLatShared<NB>, TaylorShared<NB>>;
+
+// v, new to the compiler: its transforms are formed where they are used instead
+// of being kept in registers over a loop.
+template <int NB, int G>
+__device__ __forceinline__ void again(float (&v)[NB * NB]) {
+#pragma unroll
+  for (int i = 0; i < NB * NB; ++i)
+    if (group_of<NB>(i) == G) asm volatile("" : "+v"(v[i]));
+}
+
+// The passes through latitudes: every vector is this wave's orders of it.
+template <int NB, int G>
+__device__ __forceinline__ void taylor_fwd_lat(TaylorLatShared<NB>& sh, int lane, int64_t p, bool ok,
+                                               const float* __restrict__ Fpart, int nchunks, int64_t P, float eps,
+                                               int k, int K, float* __restrict__ vis, float* __restrict__ saved) {
+  constexpr int N = NB * NB;
+  constexpr auto own = [](int i) { return group_of<NB>(i) == G; };
+  const int64_t q = ok ? p : 0;  // valid receiver for the loads of tail lanes
+  float Gv[N], R[N], T[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (own(i)) Gv[i] = sel0(ok, Fpart[(int64_t)i * P + q]);
+  for (int c = 1; c < nchunks; ++c) {
+    const float* src = Fpart + (int64_t)c * N * P + q;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (own(i)) Gv[i] += sel0(ok, src[(int64_t)i * P]);
+  }
+  const float scale = __builtin_ldexpf(1.0f, -k);
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (own(i)) Gv[i] *= eps * coef_weight<NB>(i);
+  if (own(0)) {
+    sh.Cb[0][lane] = Gv[0];
+    Gv[0] = 0.0f;
+  }
+#pragma unroll
+  for (int i = 1; i < N; ++i)
+    if (own(i)) Gv[i] *= scale;
+  __syncthreads();
+  const float c = sh.Cb[0][lane];
+  float* const grow = saved ? saved + (int64_t)(1 + k * N) * P + p : nullptr;
+  const auto save = [&](float* dst, const float (&v)[N]) {
+    if (!saved || !ok) return;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (own(i)) dst[(int64_t)i * P] = v[i];
+  };
+  if (saved && ok && G == 0) saved[p] = c;
+  save(grow, Gv);
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (own(i)) R[i] = i == 0 ? one_coef<NB>() : 0.0f;
+  for (int j = K; j >= 1; --j) {  // R_{j-1} = 1 + (R_j * G) / j; the first factor's mean is exact
+    if (j < K) save(grow + (int64_t)j * N * P, R);
+    again<NB, G>(Gv);
+    lat_product4<NB, G, false, TaylorLatShared<NB>::PH>(R, Gv, T, sh.product, lane);
+    const float h = 0.5f / (float)j;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (own(i)) R[i] = i == 0 ? fmaf(h, T[i], one_coef<NB>()) : h * T[i];
+  }
+  for (int j = 0; j < k; ++j) {
+    save(saved + (int64_t)(1 + j * N) * P + p, R);
+    lat_product4<NB, G, true, 1>(R, R, T, sh.square, lane);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (own(i)) R[i] = T[i];
+  }
+  if (!ok) return;
+  const float ec = expf(c);
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (own(i)) vis[(int64_t)i * P + p] = (ec * R[i]) * coef_inv<NB>(i);
+}
+
+template <int NB, int G>
+__device__ __forceinline__ void taylor_bwd_lat(TaylorLatShared<NB>& sh, int lane, int64_t p, bool ok,
+                                               const float* __restrict__ gIn, const float* __restrict__ vis,
+                                               const float* __restrict__ saved, int64_t P, float eps, int k, int K,
+                                               float* __restrict__ Wout) {
+  constexpr int N = NB * NB, PH = TaylorLatShared<NB>::PH;
+  constexpr auto own = [](int i) { return group_of<NB>(i) == G; };
+  const int64_t q = ok ? p : 0;  // valid receiver for the loads of tail lanes
+  const float ec = expf(sel0(ok, saved[q]));
+  float Eb[N], A[N], T[N], Gb[N];
+  float part = 0.0f;  // this wave's part of cbar = Vbar . V, in index order
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (!own(i)) continue;
+    const float vb = sel0(ok, gIn[(int64_t)i * P + q]);
+    part = fmaf(vb, sel0(ok, vis[(int64_t)i * P + q]), part);
+    Eb[i] = (ec * vb) * cot_scale<NB>(i);
+    Gb[i] = 0.0f;
+  }
+  sh.Cb[G][lane] = part;
+  __syncthreads();
+  const float cbar = ((sh.Cb[0][lane] + sh.Cb[1][lane]) + sh.Cb[2][lane]) + sh.Cb[3][lane];
+  // One loop over all products, so the code of one is there once: the reverse
+  // squarings Ebar_j = 2 (Ebar_{j+1} * E_j), then for j = 1 .. K, Eb being the
+  // cotangent of R_{j-1}, 2 (Rb * R_j) into Gb and (j < K) 2 (Rb * G) into Eb.
+  for (int s = 0; s < k + 2 * K - 1; ++s) {
+    const int u = s - k, j = 1 + u / 2;
+    const bool reverse = u < 0, second = !reverse && (u & 1);
+    if (!reverse && !second && j == K) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (own(i)) A[i] = i == 0 ? one_coef<NB>() : 0.0f;
+    } else {
+      const float* src = saved + (int64_t)(1 + (reverse ? k - 1 - s : second ? k : k + j) * N) * P + q;
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (own(i)) A[i] = src[(int64_t)i * P];
+    }
+    lat_product4<NB, G, false, PH, true>(A, Eb, T, sh.product, lane);
+    const float h = reverse ? 1.0f : 0.5f / (float)j;
+    if (reverse || second) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (own(i)) Eb[i] = h * T[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (own(i)) Gb[i] = fmaf(h, T[i], Gb[i]);
+    }
+  }
+  if (!ok) return;
+  const float scale = __builtin_ldexpf(1.0f, -k);
+#pragma unroll
+  for (int l = 0; l < NB; ++l) {
+#pragma unroll
+    for (int m = -l; m <= l; ++m) {
+      const int i = idx(l, m);
+      if (!own(i)) continue;
+      const float lam = eps * SHV_LAT_LAMI[l][m < 0 ? -m : m];
+      Wout[(int64_t)i * P + p] = i == 0 ? lam * (cbar * SHV_INV_SQRT_4PI) : lam * (scale * Gb[i]);
+    }
+  }
+}
 
 template <int NB, int G>
 __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane, int64_t p, bool ok,
@@ -58,7 +212,7 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
   float Gv[N], R[N], T[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) Gv[i] = sh.X[0][i][lane] * (eps * coef_weight<NB>(i));
-  const float c = Lat<NB>::USE ? Gv[0] : Gv[0] * SHV_INV_SQRT_4PI;
+  const float c = Gv[0] * SHV_INV_SQRT_4PI;
   const float scale = __builtin_ldexpf(1.0f, -k);
   Gv[0] = 0.0f;
 #pragma unroll
@@ -80,9 +234,7 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
       for (int i = 0; i < N; ++i)
         if (group_of<NB>(i) == G) dst[(int64_t)i * P] = R[i];
     }
-    // group G of 2 (R_j * G); through latitudes the second factor's mean is exact
-    if constexpr (Lat<NB>::USE) SqGroup<NB, G>::adj(Gv, R, T);
-    else SqGroup<NB, G>::adj(R, Gv, T);
+    SqGroup<NB, G>::adj(R, Gv, T);  // group G of 2 (R_j * G)
     const float h = 0.5f / (float)j;
 #pragma unroll
     for (int i = 0; i < N; ++i)
@@ -113,23 +265,29 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
     const float ec = expf(c);
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      if (group_of<NB>(i) == G) vis[(int64_t)i * P + p] = (ec * R[i]) * coef_inv<NB>(i);
+      if (group_of<NB>(i) == G) vis[(int64_t)i * P + p] = ec * R[i];
   }
 }
 
+template <int NB, int G, class... A>
+__device__ __forceinline__ void taylor_fwd(TaylorSharedOf<NB>& sh, A... a) {
+  if constexpr (Lat<NB>::USE) taylor_fwd_lat<NB, G>(sh, a...);
+  else taylor_fwd_group<NB, G>(sh, a...);
+}
+
 template <int NB>
-__global__ __launch_bounds__(SHV_BLOCK) void k_exp_taylor_fwd(const float* __restrict__ Fpart, int nchunks, int64_t P,
+__global__ __launch_bounds__(SHV_BLOCK, 2) void k_exp_taylor_fwd(const float* __restrict__ Fpart, int nchunks, int64_t P,
                                                               float eps, int k, int K, float* __restrict__ vis,
                                                               float* __restrict__ saved) {
-  __shared__ TaylorShared<NB> sh;
+  __shared__ TaylorSharedOf<NB> sh;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t p = (int64_t)blockIdx.x * 64 + lane;
   const bool ok = p < P;
   switch (wave) {
-    case 0: taylor_fwd_group<NB, 0>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
-    case 1: taylor_fwd_group<NB, 1>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
-    case 2: taylor_fwd_group<NB, 2>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
-    default: taylor_fwd_group<NB, 3>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
+    case 0: taylor_fwd<NB, 0>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
+    case 1: taylor_fwd<NB, 1>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
+    case 2: taylor_fwd<NB, 2>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
+    default: taylor_fwd<NB, 3>(sh, lane, p, ok, Fpart, nchunks, P, eps, k, K, vis, saved); break;
   }
 }
 
@@ -161,7 +319,7 @@ __device__ __forceinline__ void taylor_bwd_group(TaylorShared<NB>& sh, int lane,
   __syncthreads();
   float Eb[N], A[N], T[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) Eb[i] = (ec * sh.X[1][i][lane]) * cot_scale<NB>(i);
+  for (int i = 0; i < N; ++i) Eb[i] = ec * sh.X[1][i][lane];
   const float cbar = ((sh.Cb[0][lane] + sh.Cb[1][lane]) + sh.Cb[2][lane]) + sh.Cb[3][lane];
   // Reverse squarings: Ebar_j = 2 (Ebar_{j+1} * E_j).
   for (int j = k - 1; j >= 0; --j) {
@@ -224,26 +382,32 @@ __device__ __forceinline__ void taylor_bwd_group(TaylorShared<NB>& sh, int lane,
     for (int m = -l; m <= l; ++m) {
       const int i = idx(l, m);
       if (group_of<NB>(i) != G) continue;
-      const float lam = eps * (Lat<NB>::USE ? SHV_LAT_LAMI : SHV_PAIR)[l][m < 0 ? -m : m];
+      const float lam = eps * SHV_PAIR[l][m < 0 ? -m : m];
       Wout[(int64_t)i * P + p] = i == 0 ? lam * (cbar * SHV_INV_SQRT_4PI) : lam * (scale * Gb[i]);
     }
   }
 }
 
+template <int NB, int G, class... A>
+__device__ __forceinline__ void taylor_bwd(TaylorSharedOf<NB>& sh, A... a) {
+  if constexpr (Lat<NB>::USE) taylor_bwd_lat<NB, G>(sh, a...);
+  else taylor_bwd_group<NB, G>(sh, a...);
+}
+
 template <int NB>
-__global__ __launch_bounds__(SHV_BLOCK) void k_exp_taylor_bwd(const float* __restrict__ gIn,
+__global__ __launch_bounds__(SHV_BLOCK, 2) void k_exp_taylor_bwd(const float* __restrict__ gIn,
                                                               const float* __restrict__ vis,
                                                               const float* __restrict__ saved, int64_t P, float eps,
                                                               int k, int K, float* __restrict__ Wout) {
-  __shared__ TaylorShared<NB> sh;
+  __shared__ TaylorSharedOf<NB> sh;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t p = (int64_t)blockIdx.x * 64 + lane;
   const bool ok = p < P;
   switch (wave) {
-    case 0: taylor_bwd_group<NB, 0>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
-    case 1: taylor_bwd_group<NB, 1>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
-    case 2: taylor_bwd_group<NB, 2>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
-    default: taylor_bwd_group<NB, 3>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
+    case 0: taylor_bwd<NB, 0>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
+    case 1: taylor_bwd<NB, 1>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
+    case 2: taylor_bwd<NB, 2>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
+    default: taylor_bwd<NB, 3>(sh, lane, p, ok, gIn, vis, saved, P, eps, k, K, Wout); break;
   }
 }
 

@@ -3,7 +3,8 @@
 Counting rule: one floating-point add, multiply, square root, reciprocal
 square root or exponential = 1 flop; a fused multiply-add = 2 flops.  The
 counts are those of the minimal operation graph of the formulation the
-kernels implement (polynomial SH basis, sparse triple products); lane-level
+kernels implement (polynomial SH basis, sparse triple products up to 5 bands,
+products through latitudes above); lane-level
 overheads (index arithmetic, cross-lane reductions, tail lanes) are not
 counted.  Units: one (receiver, sphere) pair for the pair kernels, one
 receiver for the per-receiver kernels.
@@ -19,33 +20,108 @@ def _tri(n):
     return n * (n - 1) // 2
 
 
+def _basis_flops(n: int) -> int:
+    """One pair's basis: the cap's terms a_l(t), Re / Im (x + i y)^m, p_l(z)
+    and the rows rho_l^m of the orders 1 .. n - 1."""
+    cap = (1 if n > 2 else 0) + 3 * max(n - 3, 0)
+    cs = 6 * max(n - 2, 0)
+    p = (2 if n > 2 else 0) + 3 * max(n - 3, 0)
+    rows = 2 * _tri(max(n - 2, 0))              # one FMA per l >= m + 2
+    return cap + cs + p + rows
+
+
 def pair_fwd_flops(n: int) -> int:
-    geom = 20                                   # c - x, |v|^2, rsqrt, s, r/d, 1 - s^2, sqrt, u = s^2/(1+t)
-    leg = 5 * max(n - 1, 0)                     # residual Bonnet steps R_2 .. R_n
-    cap = 2 * n - 1                             # g_0 = K_0 u, g_l = K_l (R_{l+1} - R_{l-1})
-    cs = 6 * max(n - 2, 0)                      # Re/Im (x + i y)^m, m = 2 .. n-1
-    rec = 3 * max(n - 2, 0) * max(n - 1, 0) // 2  # r_l^m three-term steps
-    u = _tri(n)                                 # g_l r_l^m for l > m
-    acc = n + 3 + 4 * _tri(n)                   # m = 0 adds (compensated DC), m > 0 two FMAs each
-    return geom + leg + cap + cs + rec + u + acc
+    geom = 21                                   # c - x, |v|^2, rsqrt, s, r/d, its square, 1 - s^2, sqrt, u
+    u = _tri(max(n - 1, 0))                     # a_l rho_l^m for l > m >= 1
+    acc = 4 + 2 * (n - 1) + 4 * _tri(n)         # compensated DC, m = 0, m > 0 two FMAs each
+    return geom + _basis_flops(n) + u + acc
 
 
 def pair_bwd_flops(n: int) -> int:
-    base = 20 + 5 * max(n - 1, 0) + 2 * n - 1 + 6 * max(n - 2, 0) + 3 * max(n - 2, 0) * max(n - 1, 0) // 2
-    vw = 3 * _tri(n) + n                        # g_l r and (1 - R_l) r
-    m0 = 2 * n                                  # t-derivative sum of the m = 0 column
-    lm = 10 * _tri(n) + 2 * _tri(max(n - 1, 0))  # X, T (4 FMAs) and Z sums per (l, m >= 1)
-    comb = 4 + 18 * max(n - 1, 0)               # per-order combination into Gx, Gy, Gz, Gt
+    geom = 18
+    m0 = 2 * max(n - 1, 0)                      # f_l and h_l of order 0
+    lm = 0
+    for m in range(1, n):
+        for l in range(m, n):
+            lm += 3 + 4                         # b, X
+            lm += 1 if l == m else 2 + 1        # f; v
+            lm += 0 if l == m else 1 if l == m + 1 else 2 + (1 if (l - m) % 2 == 0 else 0)  # h
+    comb = 10 * max(n - 2, 0)                   # per-order combination into Gx, Gy
+    ends = (2 if n > 2 else 0) + 3 * max(n - 3, 0) + 5 * max(n - 1, 0) + 1  # p_l(t), Gz, Gt
     chain = 26 + 3 + 4                          # tangent projection, t chain, receiver / sphere sums
-    return base + vw + m0 + lm + comb + chain
+    return geom + _basis_flops(n) + m0 + lm + comb + ends + chain
+
+
+# Products through latitudes (6 bands and above): per row +-z or z = 0, the
+# transforms up of the factors, the Fourier product, the transform down.
+LAT_MIN_BANDS = 6
+
+
+def _lat_up_flops(n: int, eq: bool, mean: bool) -> int:
+    f = 0
+    for m in range(n):
+        terms = [0, 0]
+        for l in range(m, n):
+            odd = (l - m) % 2
+            if (l == 0 and not mean) or (eq and odd):
+                continue
+            terms[odd] += 1
+        parts = 1 if m == 0 else 2              # cosine (and sine)
+        f += parts * sum(2 * t - 1 for t in terms if t)
+        f += 0 if eq else 2 * parts             # the sum and the difference
+    return f
+
+
+def _lat_conv_flops(n: int, square: bool) -> int:
+    f = 0
+    for m in range(n):
+        if square:
+            if m == 0:
+                f += 2 + 4 * (n - 1)
+                continue
+            f += 2
+            for t in range(1, m // 2 + 1):
+                f += 8 if 2 * t < m else 8
+            f += 8 * (n - 1 - m)
+        else:
+            if m == 0:
+                f += 3 + 4 * (n - 1)
+                continue
+            f += 6 + 8 * (m - 1) + 16 * (n - 1 - m)
+    return f
+
+
+def _lat_down_flops(n: int, eq: bool) -> int:
+    f = 0
+    for m in range(n):
+        parts = 1 if m == 0 else 2
+        f += parts * (0 if eq else 2)
+        f += 2 * parts * sum(1 for l in range(m, n) if not (eq and (l - m) % 2))
+    return f
 
 
 @functools.lru_cache(maxsize=None)
-def _gaunt_counts(n: int):
+def _lat_flops(n: int, square: bool) -> int:
+    pairs, eq = (len(r) for r in _tables().lat_rows(n))
+    f = 2 * n * n
+    for count, at_eq in ((pairs, False), (eq, True)):
+        row = _lat_up_flops(n, at_eq, False) + (0 if square else _lat_up_flops(n, at_eq, True))
+        row += (1 if at_eq else 2) * _lat_conv_flops(n, square) + _lat_down_flops(n, at_eq)
+        f += count * row
+    return f
+
+
+def _tables():
     here = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
     if here not in sys.path:
         sys.path.insert(0, here)
     import gen_tables  # the library's own table generator
+    return gen_tables
+
+
+@functools.lru_cache(maxsize=None)
+def _gaunt_counts(n: int):
+    gen_tables = _tables()
     C = gen_tables.real_gaunt(n)
     sym = [(i, j, k) for (i, j, k) in C if j <= k]
     pairs = {(j, k) for (_, j, k) in sym}
@@ -59,11 +135,15 @@ def _gaunt_counts(n: int):
 
 
 def square_flops(n: int) -> int:
+    if n >= LAT_MIN_BANDS:
+        return _lat_flops(n, True)
     c = _gaunt_counts(n)
     return c["pairs"] + 2 * c["sym"]
 
 
 def square_adj_flops(n: int) -> int:
+    if n >= LAT_MIN_BANDS:
+        return _lat_flops(n, False)
     c = _gaunt_counts(n)
     off = c["upairs"] - c["diag"]
     return c["diag"] + 3 * off + 2 * c["sym"]
@@ -118,23 +198,26 @@ def shade_ch_bwd_flops(n: int, channels: int) -> int:
     return h + nbar + channels * (mv + vbar + lbar)
 
 
-def quad_nodes(n: int) -> int:
-    """Nodes of the quadrature exponential's rule (4n x 8n)."""
-    return 32 * n * n
+def _quad_flops(n: int, evaluations: int, per_node: int) -> int:
+    """Per receiver, the separable 4n x 8n rule: at each latitude
+    ``evaluations`` Fourier sums up and to the azimuths (folded into a quarter,
+    8 additions per four azimuths), ``per_node`` flops at a node, and one sum
+    back."""
+    transform = _lat_up_flops(n, False, True)   # of a pair of latitudes
+    down = _lat_down_flops(n, False)
+    azimuths = 2 * n * (2 * (2 * n - 1) + 8)
+    return 2 * n * (evaluations * transform + down) + 4 * n * ((evaluations + 1) * azimuths + 8 * n * per_node)
 
 
 def exp_quad_fwd_flops(n: int) -> int:
-    """Per receiver: f = Fhat Y over the nodes and V = (w exp f) Y^T, two
-    N x Q products, plus one exponential and one weight multiply per node."""
-    N, Q = n * n, quad_nodes(n)
-    return 2 * (2 * N * Q) + 2 * Q
+    """f at the nodes, one exponential (and the weight of the latitude, once
+    per Fourier sum) and V."""
+    return _quad_flops(n, 1, 1)
 
 
 def exp_quad_bwd_flops(n: int) -> int:
-    """Per receiver: f and g = Vbar Y, then Fbar = (w exp f g) Y^T: three
-    N x Q products, plus the exponential and two multiplies per node."""
-    N, Q = n * n, quad_nodes(n)
-    return 3 * (2 * N * Q) + 3 * Q
+    """f and g = Vbar at the nodes, exp(f) g, and Fbar."""
+    return _quad_flops(n, 2, 2)
 
 
 def exp_taylor_fwd_flops(n: int, k: int, K: int) -> int:
@@ -153,30 +236,48 @@ def exp_taylor_bwd_flops(n: int, k: int, K: int) -> int:
     return 3 * N + k * square_adj_flops(n) + (2 * K - 1) * (square_adj_flops(n) + 2 * N) + 2 * N
 
 
+@functools.lru_cache(maxsize=None)
+def _turn_flops(n: int) -> int:
+    """One rotation of a vector into a sphere's frame (or back): two turns
+    about z and two quarter turns."""
+    quarter = 2 * int((abs(_tables().quarter_turn()[:n * n, :n * n]) > 1e-12).sum()) - n * n
+    return 2 * (6 * _tri(n) + quarter)
+
+
+def _zonal_flops(n: int) -> int:
+    """A product with a zonal function in its frame: the rows up, a multiply
+    per Fourier coefficient and sign, and down."""
+    pairs, eq = (len(r) for r in _tables().lat_rows(n))
+    return (pairs * (_lat_up_flops(n, False, True) + 2 * (2 * n - 1) + _lat_down_flops(n, False) + 4 * n)
+            + eq * (_lat_up_flops(n, True, True) + 2 * n - 1 + _lat_down_flops(n, True) + n))
+
+
 def prod_fwd_flops(n: int) -> int:
-    """Per (receiver, sphere) step of the direct product chain: the pair's
-    blocker vector (the pair forward's basis work plus one LAMBDA multiply per
-    coefficient), one sparse product V * h (the generated product, which
-    returns 2 V * h) and the update V + beta/2 (2 V * h)."""
+    """Per (receiver, sphere) step of the direct product chain: from 6 bands
+    up the vector turned into the sphere's frame, multiplied by the zonal
+    blocker and turned back; below, the pair's blocker vector, one sparse
+    product V * h and the update."""
     N = n * n
+    if n >= LAT_MIN_BANDS:
+        return 60 + 2 * _turn_flops(n) + _zonal_flops(n) + 2 * N
     return pair_fwd_flops(n) + N + square_adj_flops(n) + 2 * N
 
 
 def prod_bwd_flops(n: int) -> int:
-    """Per step of the chain's adjoint: the blocker vector again, the two
-    sparse products Vbar * V_in and Vbar * h with their scale and update, the
-    pair weights W and RHO W, and the pair adjoint."""
+    """Per step of the chain's adjoint: from 6 bands up the state and its
+    cotangent turned, the zonal product's adjoint, the tangential derivatives
+    and the turn back; below, the blocker vector again, two sparse products,
+    the pair weights and the pair adjoint."""
     N = n * n
+    if n >= LAT_MIN_BANDS:
+        return 100 + 3 * _turn_flops(n) + 2 * _zonal_flops(n) + 8 * N
     return (pair_fwd_flops(n) + N) + 2 * square_adj_flops(n) + 3 * N + 2 * N + pair_bwd_flops(n)
 
 
 def envmap_pixel_flops(n: int) -> int:
-    """One map pixel: sin and cos of its azimuth, the direction (3), the
-    polynomial SH basis (powers of x + i y, three-term recurrences in z, one
-    normalising multiply per coefficient) and one FMA per coefficient."""
-    N = n * n
-    basis = 6 * max(n - 1, 0) + 3 * n * (n - 1) // 2 + N
-    return 2 + 3 + basis + 2 * N
+    """One map pixel: 2n - 1 FMAs, and a fourth (rows of a block share it) of
+    its column's sine and cosine and their 2n - 4 multiples."""
+    return 2 * (2 * n - 1) + (4 + 6 * max(n - 2, 0)) // 4
 
 
 # Bytes each kernel must move to / from HBM per unit (FP32).
