@@ -85,8 +85,8 @@ typedef int32_t shv_status;
                                       truncated SH products of Eq. 12, V = V'_1 * V'_2 * ... * V'_S,
                                       left to right in sphere order, of the projected floored
                                       blockers of Eq. 13 (e^-eps on each sphere's cone, 1 elsewhere;
-                                      a large eps gives Eq. 12's binary blockers).  Costs one Gaunt
-                                      product per pair forward and three in the adjoint (which runs
+                                      a large eps gives Eq. 12's binary blockers).  Costs one
+                                      truncated product per pair forward and three in the adjoint (which runs
                                       the chain again to record its states in the workspace,
                                       S * N * P floats).  n_squarings is unused; no other flag may
                                       be set.  Only sh_visibility_forward / sh_visibility_backward
@@ -442,8 +442,10 @@ shv_status shv_batch_table_build(const shv_scene* scenes, int32_t n_scenes, void
  * blocks); exp[0][n] / exp[1][n]: the exponential launches of
  * those scenes using the one-wave / four-wave layout (the layout the flags
  * select, else one receiver per lane up to 6 bands and four waves per 64
- * receivers at 7 and 8; a single-scene call takes one receiver per lane up to
- * 6 bands only from 65,536 receivers; both layouts give identical bits);
+ * receivers at 7 and 8, whose kernels take one receiver per lane themselves
+ * once the group reaches 98,304 receivers; a single-scene call takes one
+ * receiver per lane from 65,536 receivers up to 6 bands and from 98,304 at 7
+ * and 8; both layouts give identical bits);
  * finalize: the closing reductions of all scenes.  Index 0 is unused and
  * must be 0.  A group with 0 blocks is not launched. */
 typedef struct shv_batch_grid {

@@ -3,7 +3,7 @@
 // V = V'_1 * V'_2 * ... * V'_S: truncated SH products (Eqs. 6-7) of the
 // projected floored blockers V'_i (Eq. 13), taken left to right in sphere
 // order (truncated products are not associative, so the order is part of the
-// result).  With h_i = LAMBDA (.) F'_i, the pair's log-cap vector without the
+// result).  With h_i = PAIR (.) F'_i, the pair's log-cap vector without the
 // factor eps (F'_i exactly as the pair kernels form it), V'_i has the
 // coefficients sqrt(4 pi) e_0 + beta h_i with beta = 1 - e^-eps.  A product
 // with the constant 1 is exact under truncation, so each step is
@@ -11,7 +11,7 @@
 // The adjoint of one step, with Vb the cotangent of its output:
 //   hbar_i = beta (Vb * V_in),      Vb_in = Vb + beta (Vb * h_i)
 // (the triple-product tensor is symmetric in its three indices).  hbar_i
-// becomes the pair weights W_lm = LAMBDA_lm hbar_lm of the pair adjoint.
+// becomes the pair weights W_lm = PAIR_lm hbar_lm of the pair adjoint.
 //
 // From 6 bands up the products are taken in the sphere's frame (below); up to
 // 5 bands as follows.
@@ -176,7 +176,7 @@ __device__ __forceinline__ void prod_bwd_group(ProdBwdShared<NB>& sh, int lane, 
     SqGroup<NB, G>::adj(Vb, A, T);  // group G of 2 (Vb * V_in)
     const PairGeom geo = pair_geom(px, py, pz, sph[s]);
     {
-      // This wave's share of the pair weights: W_lm = LAMBDA_lm hbar_lm on
+      // This wave's share of the pair weights: W_lm = PAIR_lm hbar_lm on
       // its output group, 0 elsewhere (the pair adjoint is linear in W).
       float W[N], W0[NB];
 #pragma unroll

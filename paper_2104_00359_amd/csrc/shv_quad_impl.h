@@ -3,7 +3,7 @@
 // taken with a fixed quadrature.  A selectable accuracy mode; it changes the
 // result.
 //
-//   F = eps * lambda * (sum of the sphere-chunk partials)   (as in the squaring path)
+//   F = eps * pair * (sum of the sphere-chunk partials)   (as in the squaring path)
 //   c = F_0 / sqrt(4 pi),  f_q = sum_{i >= 1} F_i y_i(w_q)
 //   V = exp(c) sum_q w_q exp(f_q) y(w_q)
 // over the product rule of degree 8n - 1: 4n Gauss-Legendre latitudes times 8n
@@ -19,7 +19,7 @@
 //
 // Adjoint for Vbar: Fbar_0 = (sum_j Vbar_j V_j) / sqrt(4 pi) and, for i >= 1,
 //   Fbar_i = exp(c) sum_q w_q exp(f_q) g_q y_i(w_q),  g_q = sum_j Vbar_j y_j(w_q),
-// g by the same two steps as f; W = eps * lambda * Fbar feeds the pair adjoint.
+// g by the same two steps as f; W = eps * pair * Fbar feeds the pair adjoint.
 //
 // Layout: one receiver per lane, the latitudes dealt to the eight waves of a
 // block (four at 1 band), whose partial sums are added in wave order through
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(64 * Quad<NB>::WAVES, 4) void k_exp_quad_fwd(const 
   });
 }
 
-// Adjoint: gV, vis, saved F [N][P] -> W = eps lambda Fbar [N][P].
+// Adjoint: gV, vis, saved F [N][P] -> W = eps pair Fbar [N][P].
 template <int NB>
 __global__ __launch_bounds__(64 * Quad<NB>::WAVES, 4) void k_exp_quad_bwd(const float* __restrict__ gV,
                                                                           const float* __restrict__ vis,
