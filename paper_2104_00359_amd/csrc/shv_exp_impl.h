@@ -299,8 +299,8 @@ __global__ __launch_bounds__(SHV_BLOCK, Fwd1Waves<NB>::VALUE) void k_exp_fwd(
 
 // At 7 and 8 bands the one-wave adjoint keeps E_j in LDS, one column per lane:
 // with it the cotangent, the outputs and one row's Fourier coefficients are all
-// the registers hold, 256 and two waves per SIMD instead of 390 and one (222 us
-// for 262,144 receivers at 8 bands, k = 4; four waves per receiver take 288).
+// the registers hold, 256 and two waves per SIMD instead of 390 and one (203 us
+// at best for 262,144 receivers at 8 bands, k = 4; four waves per receiver take 288).
 // What bounds it is the FP32 issue of the rows: a wave issues one instruction
 // in about 5 cycles, and two waves share a SIMD.
 template <int NB>
@@ -383,19 +383,27 @@ __device__ __forceinline__ void exp_bwd1_item(const float* __restrict__ gIn, con
   }
   const float c = saved[p];
   const float ec = expf(c);
-  const float cbar = cbar_canonical<NB>(Eb, E);  // d/dc of exp(c) E_k . Vbar = V . Vbar
-  if (k == 0) {  // E_0 = V / exp(c) when there is no squaring
+  float cbar = cbar_canonical<NB>(Eb, E);  // d/dc of exp(c) E_k . Vbar = V . Vbar
+  // formed here: the epilogue alone uses it, and the compiler would otherwise move
+  // it behind the loop and hold V and Vbar, spilled, over it
+  asm volatile("" : "+v"(cbar));
+  const int col = threadIdx.x & 63;
+  // E_0 = V / exp(c) when there is no squaring.  With E_j in LDS it goes there: a way
+  // out of its own for k = 0 is laid out behind the loop and holds V and Vbar, too.
+  if (k == 0) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       E[i] = (E[i] / ec) * coef_scale<NB>(i);
-      Eb[i] = (ec * Eb[i]) * cot_scale<NB>(i);
+      if constexpr (Bwd1Lds<NB>::USE) El[i][col] = E[i];
+      else Eb[i] = (ec * Eb[i]) * cot_scale<NB>(i);
     }
-    exp_epilogue<NB>(E, Eb, cbar, eps, k, P, p, Wout, [](int) { return true; });
-    return;
+    if constexpr (!Bwd1Lds<NB>::USE) {
+      exp_epilogue<NB>(E, Eb, cbar, eps, k, P, p, Wout, [](int) { return true; });
+      return;
+    }
   }
 #pragma unroll
   for (int i = 0; i < N; ++i) Eb[i] = (ec * Eb[i]) * cot_scale<NB>(i);
-  const int col = threadIdx.x & 63;
   for (int j = k - 1; j >= 0; --j) {
     const int64_t Pj = Bwd1Lds<NB>::USE ? fresh(P) : P;
     const float* src = saved + (int64_t)(1 + j * N) * Pj + p;
