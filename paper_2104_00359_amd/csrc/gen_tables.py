@@ -499,6 +499,12 @@ def emit_quad(L):
 
 # ----------------------------------------------------------------- emission
 
+def float32_rest(x: float) -> float:
+    """What the nearest float32 leaves of x."""
+    import struct
+    return x - struct.unpack("f", struct.pack("f", x))[0]
+
+
 def flit(x: float) -> str:
     """float literal that round-trips the nearest float32."""
     import struct
@@ -525,6 +531,7 @@ def emit_constants(path):
     table2("SHV_RHO", rho)
     pair, row, row_k, row_0, cap_b, leg_b = pair_constants()
     table2("SHV_PAIR", pair)
+    table2("SHV_PAIR_LO", [[float32_rest(v) for v in r] for r in pair])
     table2("SHV_ROW", row)
     for name, t in (("SHV_ROW_K", row_k), ("SHV_ROW_0", row_0), ("SHV_CAP_B", cap_b), ("SHV_LEG_B", leg_b)):
         lines.append(f"static constexpr float {name}[{MAX_BANDS}] = {{" + ", ".join(flit(v) for v in t) + "};")

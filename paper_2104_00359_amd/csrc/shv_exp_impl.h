@@ -136,8 +136,10 @@ __device__ __forceinline__ float cbar_canonical(const float* vb, const float* v)
 }
 
 // PAIR_i, times the coefficient's scale where products go through latitudes.
+// The DC coefficient's is PAIR_0 / sqrt(4 pi) = -1/2, which makes it c itself.
 template <int NB>
 __device__ __forceinline__ float coef_weight(int i) {
+  if (i == 0) return SHV_LAT_LAM[0][0];
   if constexpr (!Lat<NB>::USE) return coef_pair(i);
   int l = 0;
   while ((l + 1) * (l + 1) <= i) ++l;
@@ -145,13 +147,29 @@ __device__ __forceinline__ float coef_weight(int i) {
   return SHV_LAT_LAM[l][m < 0 ? -m : m];
 }
 
+// F_i of one summed F'_i (c for i = 0).  A rounding of eps * weight, or of the
+// weight, would be the same for every receiver, and where many caps overlap
+// exp(c) and the squarings turn 1e-7 of it into 1e-5 of V: so eps is a factor of
+// its own and, below 6 bands, PAIR has its rest to the next float.  20,000
+// receivers x 323 spheres of a body at 3 bands, all outputs' error against 64
+// bits: 6.6e-6 with one product, 2.5e-6 with eps apart.
+template <int NB>
+__device__ __forceinline__ float weighted(float v, int i, float eps) {
+  const float w = coef_weight<NB>(i);
+  if (Lat<NB>::USE || i == 0) return (v * w) * eps;
+  int l = 0;
+  while ((l + 1) * (l + 1) <= i) ++l;
+  const int m = i - l * l - l;
+  return fmaf(v, w, v * SHV_PAIR_LO[l][m < 0 ? -m : m]) * eps;
+}
+
 // E_0 from the summed F' of one receiver (in place): returns c.
 template <int NB>
 __device__ __forceinline__ float exp_prologue(float (&E)[NB * NB], float eps, int k) {
   constexpr int N = NB * NB;
 #pragma unroll
-  for (int i = 0; i < N; ++i) E[i] *= eps * coef_weight<NB>(i);
-  const float c = Lat<NB>::USE ? E[0] : E[0] * SHV_INV_SQRT_4PI;
+  for (int i = 0; i < N; ++i) E[i] = weighted<NB>(E[i], i, eps);
+  const float c = E[0];
   const float scale = __builtin_ldexpf(1.0f, -k);
   float sig = 0.0f, sigm = 0.0f;  // scaled: sums over m = 0 and m != 0, |G|^2 / (8 pi) = sig / 2 + sigm
 #pragma unroll

@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * Quad<NB>::WAVES, 4) void k_exp_quad_fwd(const 
   for (int i = wave; i < N; i += W) {
     float v = Fpart[(int64_t)i * P + q];
     for (int c = 1; c < nchunks; ++c) v += Fpart[((int64_t)c * N + i) * P + q];
-    v *= eps * shv_coef_lam[i];
+    v = (v * shv_coef_lam[i]) * eps;
     if (saved && ok) saved[(int64_t)i * P + p] = v;
     if (i == 0) sh.c[lane] = v * SHV_INV_SQRT_4PI;
     sh.in.F[i][lane] = v * (shv_coef_norm[i] * kLog2e);

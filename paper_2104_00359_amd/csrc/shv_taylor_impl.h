@@ -78,7 +78,7 @@ __device__ __forceinline__ void taylor_fwd_lat(TaylorLatShared<NB>& sh, int lane
   const float scale = __builtin_ldexpf(1.0f, -k);
 #pragma unroll
   for (int i = 0; i < N; ++i)
-    if (own(i)) Gv[i] *= eps * coef_weight<NB>(i);
+    if (own(i)) Gv[i] = weighted<NB>(Gv[i], i, eps);
   if (own(0)) {
     sh.Cb[0][lane] = Gv[0];
     Gv[0] = 0.0f;
@@ -211,8 +211,8 @@ __device__ __forceinline__ void taylor_fwd_group(TaylorShared<NB>& sh, int lane,
   int b = 1;  // next exchange buffer
   float Gv[N], R[N], T[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) Gv[i] = sh.X[0][i][lane] * (eps * coef_weight<NB>(i));
-  const float c = Gv[0] * SHV_INV_SQRT_4PI;
+  for (int i = 0; i < N; ++i) Gv[i] = weighted<NB>(sh.X[0][i][lane], i, eps);
+  const float c = Gv[0];
   const float scale = __builtin_ldexpf(1.0f, -k);
   Gv[0] = 0.0f;
 #pragma unroll

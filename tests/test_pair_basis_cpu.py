@@ -64,3 +64,13 @@ def test_pair_basis(l):
     da = -np.ones_like(t) if l == 0 else polynomial.polyval(t, polynomial.polyder(
         polynomial.polymul([1, 0, -1], _q(l, 1) / _q(l, 1)[-1])))
     np.testing.assert_allclose(-(l + 1) * _monic(l, t), da, rtol=0, atol=1e-12 * np.abs(da).max())
+
+
+def test_weights_are_exact_to_two_floats():
+    """PAIR and its rest add up to the 64-bit factor (two 24-bit significands: 2^-48
+    relative), and the DC factor over sqrt(4 pi) is exactly -1/2."""
+    for l in range(B):
+        for m in range(l + 1):
+            hi, lo = np.float32(PAIR[l][m]), np.float32(gt.float32_rest(PAIR[l][m]))
+            assert abs(float(hi) + float(lo) - PAIR[l][m]) <= 2.0 ** -48 * abs(PAIR[l][m])
+    assert np.float32(PAIR[0][0] / math.sqrt(4 * math.pi)) == np.float32(-0.5)
